@@ -29,34 +29,29 @@ namespace {
 
 using zc = std::complex<double>;
 
-// H[:, j] = a + b (device, j+1 entries); then hsub = ||w|| and its inverse for the scaling
 // Arnoldi column of step j (nj = j + 1 basis vectors): hcol = (2 I - G) h1, with h1 = V^H w and
 // G = V^H V (Hermitian; column l of G holds v_i^H v_l for i <= l).  This is classical Gram-Schmidt
 // with one reorthogonalisation, whose second-pass dots V^H (w - V h1) = h1 - G h1 come from the
 // Gram matrix rather than from a second pass over the basis.
-__global__ void fom_gram_kernel(const z64 *G, int ld, int nj, const z64 *h1, z64 *hcol)
+// One block, bound by the latency of a row's dependent loads: eight lanes share a row (one lane per
+// row took 11 us at 20 vectors).
+__global__ void __launch_bounds__(256) fom_gram_kernel(const z64 *G, int ld, int nj, const z64 *h1, z64 *hcol)
 {
-    for (int i = threadIdx.x; i < nj; i += blockDim.x) {
+    const int q = threadIdx.x & 7;
+    for (int i0 = 0; i0 < nj; i0 += 32) {  // uniform: every lane takes part in the exchanges
+        const int i = i0 + (int)(threadIdx.x >> 3);
         z64 acc = {0.0, 0.0};
-        for (int l = 0; l < nj; ++l) {
-            const z64 g = l >= i ? G[(size_t)l * ld + i] : conj(G[(size_t)i * ld + l]);
-            acc = acc + g * h1[l];
+        if (i < nj)
+            for (int l = q; l < nj; l += 8) {
+                const z64 g = l >= i ? G[(size_t)l * ld + i] : conj(G[(size_t)i * ld + l]);
+                acc = acc + g * h1[l];
+            }
+#pragma unroll
+        for (int w = 4; w > 0; w >>= 1) {
+            acc.r += __shfl_xor(acc.r, w, 8);
+            acc.i += __shfl_xor(acc.i, w, 8);
         }
-        hcol[i] = z64{2.0 * h1[i].r - acc.r, 2.0 * h1[i].i - acc.i};
-    }
-}
-
-__global__ void fom_norm_kernel(const z64 *partials, int nb, z64 *hsub, z64 *inv)
-{
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) acc += partials[i].r;
-    __shared__ double lds[4];
-    double v[1] = {acc};
-    block_sum<1>(v, lds);
-    if (threadIdx.x == 0) {
-        const double h = sqrt(v[0]);
-        *hsub = {h, 0.0};
-        *inv = {h > 0.0 ? 1.0 / h : 0.0, 0.0};
+        if (i < nj && q == 0) hcol[i] = z64{2.0 * h1[i].r - acc.r, 2.0 * h1[i].i - acc.i};
     }
 }
 
@@ -68,12 +63,33 @@ template <> __device__ __forceinline__ float2 scaled<float2>(float2 t, double s)
     return make_float2((float)(s * t.x), (float)(s * t.y));
 }
 
-// v = w * (*inv)  (inv on the device) or v = w * a
+// v = w * a
 template <typename T>
-__global__ void fom_scale_kernel(const T *w, const z64 *inv, double a, T *v, int64_t n)
+__global__ void fom_scale_kernel(const T *w, double a, T *v, int64_t n)
 {
-    const double s = inv ? inv->r : a;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+        v[e] = scaled<T>(w[e], a);
+}
+
+// *hsub = h = ||w|| from the nb partial sums of |w|^2, v = w / h (0 for h = 0).  Every block adds the
+// partials itself, in one order (16 KiB from L2 at most): a launch for the norm alone cost 4.8 us a step.
+template <typename T>
+__global__ void __launch_bounds__(256) fom_norm_scale_kernel(const T *w, const z64 *partials, int nb, z64 *hsub, T *v,
+                                                             int64_t n)
+{
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < nb; i += 256) acc += partials[i].r;
+    __shared__ double lds[4], inv;
+    double sum[1] = {acc};
+    block_sum<1>(sum, lds);
+    if (threadIdx.x == 0) {
+        const double h = sqrt(sum[0]);
+        inv = h > 0.0 ? 1.0 / h : 0.0;
+        if (blockIdx.x == 0) *hsub = {h, 0.0};
+    }
+    __syncthreads();
+    const double s = inv;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256)
         v[e] = scaled<T>(w[e], s);
 }
 
@@ -285,13 +301,13 @@ sgn_status restarted_arnoldi(sgn_lattice l, double mu, const void *b, void *x, c
             st->nshift = ns;
         }
         // workspace: basis V_{k+1}, w, t, x_int, canonical r (from the arena)
-        const size_t hbytes = sizeof(z64) * ((size_t)ld * k + 3 * (size_t)ld + 4 + (size_t)ld * ld);
+        const size_t hbytes = sizeof(z64) * ((size_t)ld * k + 3 * (size_t)ld + (size_t)ld * ld);
         char *arena = static_cast<char *>(ctx.ensure_arena((size_t)(k + 1) * b64 + 3 * b64 + c64 + hbytes));
         char *Vb = arena;
         char *w = Vb + (size_t)(k + 1) * b64, *t = w + b64, *xi = t + b64, *rcan = xi + b64;
         z64 *Hd = reinterpret_cast<z64 *>(rcan + c64);  // column-major (k+1) x k
-        z64 *h1 = Hd + (size_t)ld * k, *cd = h1 + ld, *scal = cd + ld;  // scal: hsub, inv
-        z64 *zd = scal + 4;  // GMRES: the seed's residual z in the basis V_{k+1} (ld entries)
+        z64 *h1 = Hd + (size_t)ld * k, *cd = h1 + ld;
+        z64 *zd = cd + ld;  // GMRES: the seed's residual z in the basis V_{k+1} (ld entries)
         z64 *Gd = zd + ld;   // Gram matrix V^H V of the cycle's basis, column-major ld x ld (upper triangle)
         bool lo = false;                   // this cycle runs in FP32 (basis slots of b32 bytes)
         sgn_prec sp = SGN_PREC_F64;        // stencil precision of this cycle
@@ -351,17 +367,16 @@ sgn_status restarted_arnoldi(sgn_lattice l, double mu, const void *b, void *x, c
                 // (FP64 sums also for an FP32 basis): h1 = V^H w together with the Gram column
                 // V^H v_j, the column h = (2 I - G) h1, then w -= V h with the partials of ||w||^2
                 gram_dots(Vb, j + 1, w, Vj(j), n, h1, Gd + (size_t)j * ld, ctx, s, lo);
-                hipLaunchKernelGGL(fom_gram_kernel, dim3(1), dim3(64), 0, s, (const z64 *)Gd, ld, j + 1,
+                hipLaunchKernelGGL(fom_gram_kernel, dim3(1), dim3(256), 0, s, (const z64 *)Gd, ld, j + 1,
                                    (const z64 *)h1, Hd + (size_t)j * ld);
                 const int nb = combine_norm(w, Vb, j + 1, Hd + (size_t)j * ld, n, part, s, lo);
-                hipLaunchKernelGGL(fom_norm_kernel, dim3(1), dim3(256), 0, s, part, nb, Hd + (size_t)j * ld + j + 1,
-                                   scal + 1);
+                const int nsb = std::min(nvb, 512);
                 if (lo)
-                    hipLaunchKernelGGL(fom_scale_kernel<float2>, dim3(nvb), dim3(256), 0, s, (const float2 *)w,
-                                       (const z64 *)(scal + 1), 0.0, (float2 *)Vj(j + 1), n);
+                    hipLaunchKernelGGL(fom_norm_scale_kernel<float2>, dim3(nsb), dim3(256), 0, s, (const float2 *)w,
+                                       (const z64 *)part, nb, Hd + (size_t)j * ld + j + 1, (float2 *)Vj(j + 1), n);
                 else
-                    hipLaunchKernelGGL(fom_scale_kernel<double2>, dim3(nvb), dim3(256), 0, s, (const double2 *)w,
-                                       (const z64 *)(scal + 1), 0.0, (double2 *)Vj(j + 1), n);
+                    hipLaunchKernelGGL(fom_norm_scale_kernel<double2>, dim3(nsb), dim3(256), 0, s, (const double2 *)w,
+                                       (const z64 *)part, nb, Hd + (size_t)j * ld + j + 1, (double2 *)Vj(j + 1), n);
                 SGN_HIP(hipGetLastError());
                 ++steps;
             }
@@ -438,10 +453,10 @@ sgn_status restarted_arnoldi(sgn_lattice l, double mu, const void *b, void *x, c
                 } else if (rnorm > 0.0) {  // scaled straight into V_0 below
                     if (lo)
                         hipLaunchKernelGGL(fom_scale_kernel<float2>, dim3(nvb), dim3(256), 0, s, (const float2 *)w,
-                                           (const z64 *)nullptr, 1.0 / rnorm, (float2 *)Vj(0), n);
+                                           1.0 / rnorm, (float2 *)Vj(0), n);
                     else
                         hipLaunchKernelGGL(fom_scale_kernel<double2>, dim3(nvb), dim3(256), 0, s, (const double2 *)w,
-                                           (const z64 *)nullptr, 1.0 / rnorm, (double2 *)Vj(0), n);
+                                           1.0 / rnorm, (double2 *)Vj(0), n);
                     SGN_HIP(hipGetLastError());
                 }
             } else if (project && !exact) {
@@ -479,7 +494,7 @@ sgn_status restarted_arnoldi(sgn_lattice l, double mu, const void *b, void *x, c
             if (rnorm != 1.0 && (!gmres || project)) {
                 if (lo)
                     hipLaunchKernelGGL(fom_scale_kernel<float2>, dim3(nvb), dim3(256), 0, s, (const float2 *)Vj(0),
-                                       (const z64 *)nullptr, 1.0 / rnorm, (float2 *)Vj(0), n);
+                                       1.0 / rnorm, (float2 *)Vj(0), n);
                 else
                     scale64({1.0 / rnorm, 0.0}, Vj(0), Vj(0), n, s);
                 SGN_HIP(hipGetLastError());

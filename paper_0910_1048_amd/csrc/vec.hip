@@ -111,36 +111,29 @@ __global__ void cvt32to64(const float4 *__restrict__ x, double2 *__restrict__ y,
     }
 }
 
-// grid (nbx, m): partials[i * nbx + bx] = sum conj(X_i) y over the block's slice
-// (T = double2 or float2; FP64 accumulation either way)
-constexpr int kDotGroup = 8;   // dot products per pass of y
-constexpr int kDotBlocks = 2048;  // blocks per pass (grid-stride over the elements; enough loads in flight)
+constexpr int kDotGroup = 8;      // vectors of one wavefront of a multi-vector dot product
+constexpr int kDotWaves = 8;      // most wavefronts (groups) per block
+constexpr int kDotBlocks = 2048;  // most blocks of a multi-vector reduction
 
-// partials[i * gridDim.x + b] = sum over block b's slice of conj(X_i) . y for the kDotGroup
-// vectors i of group blockIdx.y (fewer in the last group); y is read once per group
-template <typename T>
-__global__ void __launch_bounds__(256) mdot_kernel(const T *X, const T *y, int64_t n, int m, z64 *partials)
+// Sums of NV values (a power of two, at most 64) over a wavefront, the sums scattered over the lanes:
+// afterwards v[0] of lane l holds the wavefront's sum of value l / (64 / NV).  Each halving step exchanges
+// half of the values that are left, NV + log2(64 / NV) - 1 exchanges instead of the 6 NV of one tree per value.
+template <int NV>
+__device__ __forceinline__ void wave_sum_scatter(double (&v)[NV])
 {
-    const int i0 = blockIdx.y * kDotGroup;
-    const int cnt = min(kDotGroup, m - i0);
-    double acc[2 * kDotGroup];
+    const int lane = threadIdx.x & 63;
+    int mask = 32;
 #pragma unroll
-    for (int c = 0; c < 2 * kDotGroup; ++c) acc[c] = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const T b = y[e];
+    for (int half = NV / 2; half > 0; half >>= 1, mask >>= 1) {
+        const bool up = lane & mask;
 #pragma unroll
-        for (int c = 0; c < kDotGroup; ++c) {
-            if (c < cnt) {
-                const T a = X[(int64_t)(i0 + c) * n + e];
-                acc[2 * c] += (double)a.x * b.x + (double)a.y * b.y;
-                acc[2 * c + 1] += (double)a.x * b.y - (double)a.y * b.x;
-            }
+        for (int i = 0; i < half; ++i) {
+            const double keep = up ? v[i + half] : v[i], send = up ? v[i] : v[i + half];
+            v[i] = keep + __shfl_xor(send, mask, 64);
         }
     }
-    __shared__ double lds[2 * kDotGroup * 4];
-    block_sum<2 * kDotGroup>(acc, lds);
-    if (threadIdx.x == 0)
-        for (int c = 0; c < cnt; ++c) partials[(int64_t)(i0 + c) * gridDim.x + blockIdx.x] = {acc[2 * c], acc[2 * c + 1]};
+#pragma unroll
+    for (; mask > 0; mask >>= 1) v[0] += __shfl_xor(v[0], mask, 64);
 }
 
 // conj(a) . b accumulated in FP64: one complex entry (double2, float2) or two (float4)
@@ -160,41 +153,46 @@ __device__ __forceinline__ void acc_cdot(float4 a, float4 b, double &re, double 
     im += (double)a.x * b.y - (double)a.y * b.x + (double)a.z * b.w - (double)a.w * b.z;
 }
 
-// Two right-hand sides in one pass over X: partials[i * gridDim.x + b] for conj(X_i) . y1 and
-// partials[(m + i) * gridDim.x + b] for conj(X_i) . y2, the kDotGroup vectors i of group blockIdx.y
-// (T = float4 takes complex64 entries two at a time: n counts such pairs)
-template <typename T>
-__global__ void __launch_bounds__(256) mdot2_kernel(const T *X, const T *y1, const T *y2, int64_t n, int m,
-                                                    z64 *partials)
+// conj(X_i) . y_q for the m vectors X_i and NY vectors y_q (one or two): partials[(q m + i) * gridDim.x + b] is
+// block b's part.  (T = float4 takes complex64 entries two at a time: n counts such pairs.)  Every wavefront has
+// a group of at most kDotGroup vectors of its own (the m vectors dealt evenly over the ng groups) and walks the
+// same 64 elements as the block's other wavefronts, so y_q comes from memory once for up to kDotWaves groups.
+// HBM-bound if the loads of a whole group are in flight together: a group of fewer vectors reads its last one
+// again (from L1) instead of branching around the load, since with a branch per vector each load waited for the
+// one before it.  Measured on 16^4 FP64, mean over the 1..40 vectors of a restart cycle (283 MB): 139 us with a
+// branch per vector and blocks of one group, 65 us now (4.4 TB/s; a large copy reaches 5.3).
+template <typename T, int NY>
+__global__ void __launch_bounds__(64 * kDotWaves) mdot_kernel(const T *X, const T *y1, const T *y2, int64_t n, int m,
+                                                              int ng, z64 *partials)
 {
-    const int i0 = blockIdx.y * kDotGroup;
-    const int cnt = min(kDotGroup, m - i0);
-    double acc[4 * kDotGroup];
+    constexpr int NV = 2 * NY * kDotGroup;
+    const int g = blockIdx.y * kDotWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int per = (m + ng - 1) / ng, i0 = g * per;
+    if (i0 >= m) return;  // a whole wavefront (no barrier in this kernel)
+    const int cnt = min(per, m - i0);
+    const T *Xg = X + (int64_t)i0 * n;
+    int64_t off[kDotGroup];
 #pragma unroll
-    for (int c = 0; c < 4 * kDotGroup; ++c) acc[c] = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const T b1 = y1[e], b2 = y2[e];
+    for (int c = 0; c < kDotGroup; ++c) off[c] = (int64_t)min(c, cnt - 1) * n;
+    double acc[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) acc[c] = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * 64 + lane; e < n; e += (int64_t)gridDim.x * 64) {
+        const T b1 = y1[e];
+        T b2{}, a[kDotGroup];
+        if constexpr (NY == 2) b2 = y2[e];
+#pragma unroll
+        for (int c = 0; c < kDotGroup; ++c) a[c] = Xg[off[c] + e];
 #pragma unroll
         for (int c = 0; c < kDotGroup; ++c) {
-            if (c < cnt) {
-                const T a = X[(int64_t)(i0 + c) * n + e];
-                acc_cdot(a, b1, acc[2 * c], acc[2 * c + 1]);
-                acc_cdot(a, b2, acc[2 * kDotGroup + 2 * c], acc[2 * kDotGroup + 2 * c + 1]);
-            }
+            acc_cdot(a[c], b1, acc[2 * c], acc[2 * c + 1]);
+            if constexpr (NY == 2) acc_cdot(a[c], b2, acc[2 * kDotGroup + 2 * c], acc[2 * kDotGroup + 2 * c + 1]);
         }
     }
-    __shared__ double lds[4 * kDotGroup * 4];
-    block_sum<4 * kDotGroup>(acc, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int c = 0; c < kDotGroup; ++c) {  // constant indices keep acc in registers
-            if (c < cnt) {
-                partials[(int64_t)(i0 + c) * gridDim.x + blockIdx.x] = {acc[2 * c], acc[2 * c + 1]};
-                partials[(int64_t)(m + i0 + c) * gridDim.x + blockIdx.x] = {acc[2 * kDotGroup + 2 * c],
-                                                                             acc[2 * kDotGroup + 2 * c + 1]};
-            }
-        }
-    }
+    wave_sum_scatter<NV>(acc);
+    const int k = lane / (64 / NV), q = k / (2 * kDotGroup), c = (k / 2) % kDotGroup;
+    if (lane % (64 / NV) == 0 && c < cnt)
+        reinterpret_cast<double *>(partials)[2 * ((int64_t)(q * m + i0 + c) * gridDim.x + blockIdx.x) + (k & 1)] = acc[0];
 }
 
 // grid (nbx, m): partials[i * nbx + bx] = {sum |X_i|^2 over the block's slice, 0}
@@ -212,7 +210,8 @@ __global__ void __launch_bounds__(256) mnorm_kernel(const T *X, int64_t n, z64 *
     if (threadIdx.x == 0) partials[(int64_t)i * gridDim.x + blockIdx.x] = {acc[0], 0.0};
 }
 
-__global__ void __launch_bounds__(256) mfinalize_kernel(const z64 *partials, int nbx, z64 *out)
+// out1[i] for i < m and out2[i - m] beyond: the sum of partials[i * nbx ...] (block i)
+__global__ void __launch_bounds__(256) mfinalize_kernel(const z64 *partials, int nbx, int m, z64 *out1, z64 *out2)
 {
     const int i = blockIdx.x;
     double re = 0.0, im = 0.0;
@@ -223,7 +222,7 @@ __global__ void __launch_bounds__(256) mfinalize_kernel(const z64 *partials, int
     __shared__ double lds[8];
     double v[2] = {re, im};
     block_sum<2>(v, lds);
-    if (threadIdx.x == 0) out[i] = {v[0], v[1]};
+    if (threadIdx.x == 0) (i < m ? out1[i] : out2[i - m]) = {v[0], v[1]};
 }
 
 template <typename T>
@@ -426,25 +425,42 @@ void convert_32_to_64(const void *x32, void *x64, int64_t S, hipStream_t s)
     SGN_HIP(hipGetLastError());
 }
 
+namespace {
+
+// Grid of mdot_kernel over n elements: groups, blocks and threads.  About 4096 wavefronts (16 per CU on 256 CUs)
+// keep enough loads in flight; more would only add partial sums.
+struct DotShape {
+    int ng, nbx, ny, threads;
+    DotShape(int64_t n, int m)
+    {
+        ng = (m + kDotGroup - 1) / kDotGroup;
+        nbx = (int)std::max<int64_t>(1, std::min<int64_t>({(n + 63) / 64, (int64_t)kDotBlocks, (int64_t)(4096 / ng)}));
+        ny = (ng + kDotWaves - 1) / kDotWaves;
+        threads = 64 * std::min(ng, kDotWaves);
+    }
+};
+
+}  // namespace
+
 size_t deflate_partials_bytes(int m, int64_t n)
 {
-    const int nbx = std::max(1, std::min(kDotBlocks, (int)((n + 255) / 256)));
-    return (size_t)std::max(m, 0) * nbx * sizeof(z64);
+    // what DotShape gives for any number of vectors up to m: m nbx <= m kDotBlocks and, as m <= 8 ng, <= 8 * 4096
+    const size_t rows = (size_t)std::max(m, 0) * std::min<int64_t>(kDotBlocks, (n + 63) / 64);
+    return std::max<size_t>(std::min<size_t>(rows, 8 * 4096), (size_t)std::max(m, 0)) * sizeof(z64);
 }
 
 void deflate_dots(const void *X, int m, const void *y, int64_t n, z64 *c_dev, Context &ctx, hipStream_t s, bool f32)
 {
     if (m <= 0) return;
-    const int nbx = std::max(1, std::min(kDotBlocks, (int)((n + 255) / 256)));
-    const int ng = (m + kDotGroup - 1) / kDotGroup;
+    const DotShape d(n, m);
     z64 *part = static_cast<z64 *>(ctx.ensure_partials(deflate_partials_bytes(m, n)));
     if (f32)
-        hipLaunchKernelGGL(mdot_kernel<float2>, dim3(nbx, ng), dim3(256), 0, s, (const float2 *)X, (const float2 *)y, n,
-                           m, part);
+        hipLaunchKernelGGL((mdot_kernel<float2, 1>), dim3(d.nbx, d.ny), dim3(d.threads), 0, s, (const float2 *)X,
+                           (const float2 *)y, (const float2 *)nullptr, n, m, d.ng, part);
     else
-        hipLaunchKernelGGL(mdot_kernel<double2>, dim3(nbx, ng), dim3(256), 0, s, (const double2 *)X, (const double2 *)y,
-                           n, m, part);
-    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part, nbx, c_dev);
+        hipLaunchKernelGGL((mdot_kernel<double2, 1>), dim3(d.nbx, d.ny), dim3(d.threads), 0, s, (const double2 *)X,
+                           (const double2 *)y, (const double2 *)nullptr, n, m, d.ng, part);
+    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part, d.nbx, m, c_dev, c_dev);
     SGN_HIP(hipGetLastError());
 }
 
@@ -454,7 +470,7 @@ void deflate_norms(const void *X, int m, int64_t n, z64 *out_dev, Context &ctx, 
     const int nbx = std::max(1, std::min(kDotBlocks, (int)((n + 255) / 256)));
     z64 *part = static_cast<z64 *>(ctx.ensure_partials((size_t)m * nbx * sizeof(z64)));
     hipLaunchKernelGGL(mnorm_kernel<double2>, dim3(nbx, m), dim3(256), 0, s, (const double2 *)X, n, part);
-    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part, nbx, out_dev);
+    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part, nbx, m, out_dev, out_dev);
     SGN_HIP(hipGetLastError());
 }
 
@@ -462,21 +478,18 @@ void gram_dots(const void *X, int m, const void *y1, const void *y2, int64_t n, 
                Context &ctx, hipStream_t s, bool f32)
 {
     if (m <= 0) return;
-    // enough blocks to keep loads in flight when there is a single group (small m)
-    const int nbx = std::max(1, std::min(kGramBlocks, (int)((n + 255) / 256)));
-    const int ng = (m + kDotGroup - 1) / kDotGroup;
-    z64 *part = static_cast<z64 *>(ctx.ensure_partials((size_t)2 * m * nbx * sizeof(z64)));
+    const DotShape d(f32 && n % 2 == 0 ? n / 2 : n, m);
+    z64 *part = static_cast<z64 *>(ctx.ensure_partials((size_t)2 * m * d.nbx * sizeof(z64)));
     if (f32 && n % 2 == 0)  // pairs of complex64 entries: 16-byte loads, as for complex128
-        hipLaunchKernelGGL(mdot2_kernel<float4>, dim3(nbx, ng), dim3(256), 0, s, (const float4 *)X, (const float4 *)y1,
-                           (const float4 *)y2, n / 2, m, part);
+        hipLaunchKernelGGL((mdot_kernel<float4, 2>), dim3(d.nbx, d.ny), dim3(d.threads), 0, s, (const float4 *)X,
+                           (const float4 *)y1, (const float4 *)y2, n / 2, m, d.ng, part);
     else if (f32)
-        hipLaunchKernelGGL(mdot2_kernel<float2>, dim3(nbx, ng), dim3(256), 0, s, (const float2 *)X, (const float2 *)y1,
-                           (const float2 *)y2, n, m, part);
+        hipLaunchKernelGGL((mdot_kernel<float2, 2>), dim3(d.nbx, d.ny), dim3(d.threads), 0, s, (const float2 *)X,
+                           (const float2 *)y1, (const float2 *)y2, n, m, d.ng, part);
     else
-        hipLaunchKernelGGL(mdot2_kernel<double2>, dim3(nbx, ng), dim3(256), 0, s, (const double2 *)X,
-                           (const double2 *)y1, (const double2 *)y2, n, m, part);
-    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part, nbx, c1_dev);
-    hipLaunchKernelGGL(mfinalize_kernel, dim3(m), dim3(256), 0, s, part + (size_t)m * nbx, nbx, c2_dev);
+        hipLaunchKernelGGL((mdot_kernel<double2, 2>), dim3(d.nbx, d.ny), dim3(d.threads), 0, s, (const double2 *)X,
+                           (const double2 *)y1, (const double2 *)y2, n, m, d.ng, part);
+    hipLaunchKernelGGL(mfinalize_kernel, dim3(2 * m), dim3(256), 0, s, part, d.nbx, m, c1_dev, c2_dev);
     SGN_HIP(hipGetLastError());
 }
 

@@ -151,3 +151,16 @@ def test_deflated_mixed_fom():
     print(f"deflated mixed FOM: vs dense {e:.2e}, cycles {st['restarts']} ({st['reliable_updates']} FP32)", flush=True)
     assert st["reliable_updates"] >= 1
     assert e < 1e-8
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32])
+@pytest.mark.parametrize("kmax", [7, 8, 9, 64, 65, 130])
+def test_basis_sizes_at_the_edges_of_the_dot_product_groups(kmax, prec):
+    # groups of 8 vectors per wavefront, 8 groups per block: the last cycle's dot products run over
+    # 1 .. kmax + 1 vectors, and a wrong one leaves the basis oblique and the residuals wrong
+    dims = (4, 4, 4, 4)
+    g = np.load(GOLD)
+    rf = sgn.sgn_rational_neuberger(16, float(g["alpha"]), float(g["beta"]))
+    b = synth.gaussian_source(dims, 0).ravel()
+    x, _ = _fom(lattice(synth.gauge_field(dims, 0.5, 0), dims), 0.3, b, rf, kmax=kmax, tol=1e-11, prec=prec)
+    assert _rel(x, g["g16_b"]) < 1e-8
