@@ -7,7 +7,8 @@
 // factor, and adds the reconstructed 4-spinor.  The chemical potential enters
 // only as the weights e^{-mu} (forward time hop) and e^{+mu} (backward time
 // hop); the adjoint H_W(mu)^H = H_W(-mu) is the same kernel with mu -> -mu.
-// Single-RHS stencil: HBM-bound, 1368 flop per site.
+// Single-RHS stencil: HBM-bound, 1368 flop per site.  On small lattices, and for fields in the canonical
+// layout, one wavefront per hop (the split kernel) instead of one thread per site.
 #include "field_io.h"
 #include "launch.h"
 
@@ -89,7 +90,7 @@ struct StencilParams {
     int tslices;     // staged kernel: t-slices per block (1, or 2: a brick of the same B sites at t and t + 1)
     int nblk_total;  // blocks of this application (sites + padding); batched launches skip the rest
     int link_ne;     // complex entries stored per link (6 or 9)
-    int tgauge;      // temporal gauge: U_t = 1 off the last time slice (the staged kernel skips those links)
+    int tgauge;      // temporal gauge: U_t = 1 off the last time slice (the staged and split kernels skip those links)
     int nrhs;        // right-hand sides of this application (staged kernel; the unstaged one uses NR)
     RhsParams rhs[kMaxRhs];
 };
@@ -716,6 +717,417 @@ __global__ void __launch_bounds__(kRegs ? kRegsMaxThreads : kStagedMaxThreads<R>
     staged_body<R, LT, kEpi, kDot, kRegs, true>(P, (int)blockIdx.x);
 }
 
+// ---------------------------------------------------------------------------- split stencil
+// Small lattices, where one thread per site leaves most of the chip idle and a launch is bound by the
+// latency of one thread's 16 loads and 8 hops in sequence: 64 sites per block of eight wavefronts, one
+// hop each (direction and sense are wave-uniform).  A wavefront loads its hop's neighbour spinor and
+// link, all in flight at once, and leaves the transported half spinor in LDS; after the barrier six
+// wavefronts take one pair of components of the 64 sites each, add the eight hops to the diagonal term in
+// the order and with the operations of the staged kernel (so the result has the same bits) and run the
+// epilogue.  Neighbours come through L2: no reuse inside the block.  One FP64 application on 8^4: 8.7 us as
+// 16 staged blocks, 4.6 us here.
+// The form for canonical fields is used at every size: it is as fast as the staged kernel on internal fields
+// (24^3 x 48: FP64 146 us against 135, FP32 61 against 58) and needs no pack and unpack passes (with them 267
+// and 130 us).
+constexpr int kSplitSites = 64, kSplitThreads = 512;
+
+// component pair C (components 2C, 2C + 1) of site s, internal layout
+__device__ __forceinline__ void load_pair(const double2 *__restrict__ p, int S, int s, int C, cpx<double> v[2])
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double2 t = ld_off(p + (size_t)(2 * C + q) * S, (uint32_t)s * 16u);
+        v[q] = {t.x, t.y};
+    }
+}
+__device__ __forceinline__ void load_pair(const float4 *__restrict__ p, int S, int s, int C, cpx<float> v[2])
+{
+    const float4 t = ld_off(p + (size_t)C * S, (uint32_t)s * 16u);
+    v[0] = {t.x, t.y};
+    v[1] = {t.z, t.w};
+}
+__device__ __forceinline__ void store_pair(double2 *__restrict__ p, int S, int s, int C, const cpx<double> v[2])
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) st_off(p + (size_t)(2 * C + q) * S, (uint32_t)s * 16u, make_double2(v[q].r, v[q].i));
+}
+__device__ __forceinline__ void store_pair(float4 *__restrict__ p, int S, int s, int C, const cpx<float> v[2])
+{
+    st_off(p + (size_t)C * S, (uint32_t)s * 16u, make_float4(v[0].r, v[0].i, v[1].r, v[1].i));
+}
+
+// Canonical fields hold a site's 12 components together (192 or 96 bytes).  A lane that loads its own site
+// 16 bytes at a time makes every load of a wavefront touch 64 cache lines, and the address unit then takes 64
+// cycles where the data would take 16.  So neighbouring lanes load consecutive 16-byte pieces of one site,
+// for each of their sites in turn, and exchange the pieces in registers (DPP within four lanes): four lanes
+// and 64-byte segments in FP64, two lanes and 32-byte segments in FP32.  Every lane must be active.
+template <int CTRL>
+__device__ __forceinline__ int dpp_quad(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;               // lane ^ 1, lane ^ 2
+constexpr int kPairFirst = 0xA0, kPairSecond = 0xF5;            // the even and the odd lane of each pair
+typedef int piece __attribute__((ext_vector_type(4)));          // 16 bytes
+
+// lanes with up = 0 keep a and receive the partner's a in b; lanes with up = 1 keep b and receive its b in a
+template <int CTRL>
+__device__ __forceinline__ void exchange(piece &a, piece &b, bool up)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int t = dpp_quad<CTRL>(up ? a[k] : b[k]);
+        if (up) a[k] = t;
+        else b[k] = t;
+    }
+}
+
+__device__ __forceinline__ void load_site_canon(const double2 *__restrict__ p, int n, cpx<double> v[12])
+{
+    const int q = threadIdx.x & 3;
+    const size_t n0 = (size_t)dpp_quad<0x00>(n) * 12 + q, n1 = (size_t)dpp_quad<0x55>(n) * 12 + q,
+                 n2 = (size_t)dpp_quad<0xAA>(n) * 12 + q, n3 = (size_t)dpp_quad<0xFF>(n) * 12 + q;
+    const piece *b = reinterpret_cast<const piece *>(p);
+    piece a[12];
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        a[4 * g] = ld_off(b + n0 + 4 * g, 0u);
+        a[4 * g + 1] = ld_off(b + n1 + 4 * g, 0u);
+        a[4 * g + 2] = ld_off(b + n2 + 4 * g, 0u);
+        a[4 * g + 3] = ld_off(b + n3 + 4 * g, 0u);
+    }
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        piece *r = a + 4 * g;
+        exchange<kQuadXor1>(r[0], r[1], q & 1);
+        exchange<kQuadXor1>(r[2], r[3], q & 1);
+        exchange<kQuadXor2>(r[0], r[2], q & 2);
+        exchange<kQuadXor2>(r[1], r[3], q & 2);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[4 * g + c] = __builtin_bit_cast(cpx<double>, r[c]);
+    }
+}
+
+__device__ __forceinline__ void split_piece(piece t, cpx<float> v[2])
+{
+    const float4 f = __builtin_bit_cast(float4, t);
+    v[0] = {f.x, f.y};
+    v[1] = {f.z, f.w};
+}
+
+__device__ __forceinline__ void load_site_canon(const float4 *__restrict__ p, int n, cpx<float> v[12])
+{
+    const int q = threadIdx.x & 1;
+    const size_t n0 = (size_t)dpp_quad<kPairFirst>(n) * 6 + q, n1 = (size_t)dpp_quad<kPairSecond>(n) * 6 + q;
+    const piece *b = reinterpret_cast<const piece *>(p);
+    piece a[6];
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        a[2 * g] = ld_off(b + n0 + 2 * g, 0u);
+        a[2 * g + 1] = ld_off(b + n1 + 2 * g, 0u);
+    }
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+        exchange<kQuadXor1>(a[2 * g], a[2 * g + 1], q);
+        split_piece(a[2 * g], v + 4 * g);
+        split_piece(a[2 * g + 1], v + 4 * g + 2);
+    }
+}
+
+// component pair C of this lane's site s
+__device__ __forceinline__ void load_pair_canon(const double2 *__restrict__ p, int s, int C, cpx<double> v[2])
+{
+    const int q = threadIdx.x & 1;
+    const piece *b = reinterpret_cast<const piece *>(p) + 2 * C + q;
+    piece a0 = ld_off(b + (size_t)dpp_quad<kPairFirst>(s) * 12, 0u);
+    piece a1 = ld_off(b + (size_t)dpp_quad<kPairSecond>(s) * 12, 0u);
+    exchange<kQuadXor1>(a0, a1, q);
+    v[0] = __builtin_bit_cast(cpx<double>, a0);
+    v[1] = __builtin_bit_cast(cpx<double>, a1);
+}
+__device__ __forceinline__ void load_pair_canon(const float4 *__restrict__ p, int s, int C, cpx<float> v[2])
+{
+    split_piece(ld_off(reinterpret_cast<const piece *>(p) + (size_t)s * 6 + C, 0u), v);
+}
+
+// neighbour of s in direction NU (forward or backward); wrap: the hop crosses the boundary
+template <int NU, bool FWD>
+__device__ __forceinline__ int hop_site(const StencilParams &P, int s, int coord, bool &wrap)
+{
+    const int L = P.L[NU], st = P.stride[NU];
+    wrap = coord == (FWD ? L - 1 : 0);
+    return FWD ? (wrap ? s - (L - 1) * st : s + st) : (wrap ? s + (L - 1) * st : s - st);
+}
+
+// chi = U (1 - gamma) psi(x + nu) or U^H (1 + gamma) psi(x - nu), the operations of hop_pair_staged
+template <int NU, bool FWD, bool kCanon, typename R, typename LT>
+__device__ __forceinline__ void split_hop(const StencilParams &P, const RhsParams &Q, int s, int coord, cpx<R> chi[6])
+{
+    bool wrap;
+    const int n = hop_site<NU, FWD>(P, s, coord, wrap);
+    const bool unit = NU == 3 && P.tgauge && !wrap;
+    cpx<R> u[9], p[12], h[6];
+    if (!unit) load_link<R>(static_cast<const LT *>(P.links), P.S, P.link_ne, NU, FWD ? s : n, u);
+    if constexpr (kCanon) load_site_canon(static_cast<const SpT<R> *>(Q.in), n, p);
+    else load_spinor(static_cast<const SpT<R> *>(Q.in), P.S, n, p);
+    project<NU, FWD>(p, h, static_cast<R>(Q.s5_in));
+    if (unit) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) chi[k] = h[k];
+    } else {
+        link_mul<!FWD>(u, h, chi);
+    }
+}
+
+// what component (spin SP, colour c) takes from a hop: the half spinor's row and phase, as in accumulate()
+template <int NU, bool FWD, int SP>
+struct HopRow {
+    static constexpr int row = SP < 2 ? SP : (NU < 2 ? 3 - SP : SP - 2);
+    static constexpr int phase = SP < 2    ? kP1
+                                 : NU == 0 ? (FWD ? kPI : kMI)
+                                 : NU == 1 ? ((SP == 2) == FWD ? kM1 : kP1)
+                                 : NU == 2 ? ((SP == 2) == FWD ? kPI : kMI)
+                                           : (FWD ? kM1 : kP1);
+};
+
+template <int NU, int C, typename R>
+__device__ __forceinline__ void split_add(cpx<R> (&acc)[2], const StencilParams &P, const RhsParams &Q, int coord,
+                                          const cpx<R> *chi /* [hop][6][kSplitSites], at this site */)
+{
+    const R kap = static_cast<R>(P.kappa);
+    const R bf = coord == P.L[NU] - 1 ? static_cast<R>(P.bcf[NU]) : R(1);
+    const R bb = coord == 0 ? static_cast<R>(P.bcf[NU]) : R(1);
+    const R wf = NU == 3 ? static_cast<R>(Q.wf_t) : R(1), wb = NU == 3 ? static_cast<R>(Q.wb_t) : R(1);
+    const cpx<R> *f = chi + (2 * NU) * 6 * kSplitSites, *b = f + 6 * kSplitSites;
+    constexpr int S0 = (2 * C) / 3, c0 = (2 * C) % 3, S1 = (2 * C + 1) / 3, c1 = (2 * C + 1) % 3;
+    using F0 = HopRow<NU, true, S0>;
+    using F1 = HopRow<NU, true, S1>;
+    using B0 = HopRow<NU, false, S0>;
+    using B1 = HopRow<NU, false, S1>;
+    acc[0] = add_ph<F0::phase>(acc[0], -kap * wf * bf, f[(3 * F0::row + c0) * kSplitSites]);
+    acc[1] = add_ph<F1::phase>(acc[1], -kap * wf * bf, f[(3 * F1::row + c1) * kSplitSites]);
+    acc[0] = add_ph<B0::phase>(acc[0], -kap * wb * bb, b[(3 * B0::row + c0) * kSplitSites]);
+    acc[1] = add_ph<B1::phase>(acc[1], -kap * wb * bb, b[(3 * B1::row + c1) * kSplitSites]);
+}
+
+// acc (the diagonal term's pair C, gamma5 of the input not yet applied) += the eight hops, in the staged
+// kernel's order
+template <int C, typename R>
+__device__ __forceinline__ void split_sum(cpx<R> (&acc)[2], const StencilParams &P, const RhsParams &Q,
+                                          const int (&c)[4], const cpx<R> *chi)
+{
+    if constexpr (C >= 3) {
+        const R s5 = static_cast<R>(Q.s5_in);
+        acc[0] = s5 * acc[0];
+        acc[1] = s5 * acc[1];
+    }
+    split_add<0, C, R>(acc, P, Q, c[0], chi);
+    split_add<1, C, R>(acc, P, Q, c[1], chi);
+    split_add<2, C, R>(acc, P, Q, c[2], chi);
+    split_add<3, C, R>(acc, P, Q, c[3], chi);
+}
+
+template <typename R, typename LT, bool kEpi, bool kDot, bool kCanon, bool kMulti>
+__device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
+{
+    const int nr = kMulti ? P.nrhs : 1;
+    if (bx >= P.nblk_sites) {  // padding of the component arrays (internal layout): keep it zero
+        const int s = P.V + (bx - P.nblk_sites) * kSplitThreads + (int)threadIdx.x;
+        for (int r = 0; r < nr; ++r) {
+            const RhsParams &Q = P.rhs[kMulti ? r : 0];
+            if (s < P.S) {
+                cpx<R> zero[12];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) zero[k] = {R(0), R(0)};
+                store_spinor(static_cast<SpT<R> *>(Q.out), P.S, s, zero);
+            }
+            if constexpr (kDot) {
+                if (threadIdx.x == 0 && Q.w) {
+                    if (Q.norm) {
+                        Q.partials[2 * bx] = {0.0, 0.0};
+                        Q.partials[2 * bx + 1] = {0.0, 0.0};
+                    } else {
+                        Q.partials[bx] = {0.0, 0.0};
+                    }
+                }
+            }
+        }
+        return;
+    }
+    __shared__ __align__(16) cpx<R> chi_lds[8 * 6 * kSplitSites];
+    __shared__ __align__(16) cpx<R> out_lds[kCanon ? 13 * kSplitSites : 1];  // rows of 12, padded by one
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int blk;
+    if (P.sched_T > 0) {  // t fastest inside each XCD's t-slab (as the staged kernel)
+        const int k = bx % 8, j = bx / 8;
+        blk = (k * P.sched_T + j % P.sched_T) * P.sched_R + j / P.sched_T;
+    } else {
+        blk = xcd_block(bx, P.nblk_sites);
+    }
+    // lanes past the last site work on it too (the register exchanges of the canonical form need every
+    // lane) and store nothing
+    const int s0 = blk * kSplitSites, s = min(s0 + lane, P.V - 1);
+    const bool valid = s0 + lane < P.V;
+    int c[4];
+    {
+        c[0] = s % P.L[0];
+        int q = s / P.L[0];
+        c[1] = q % P.L[1];
+        q /= P.L[1];
+        c[2] = q % P.L[2];
+        c[3] = q / P.L[2];
+    }
+    for (int r = 0; r < nr; ++r) {
+        const RhsParams &Q = P.rhs[kMulti ? r : 0];
+        if (r > 0) __syncthreads();  // the previous right-hand side's LDS reads are done
+        const bool mine = wave < 6;  // this wavefront finishes component pair `wave`
+        cpx<R> acc[2] = {{R(0), R(0)}, {R(0), R(0)}}, zz[2], ww[2];
+        auto load_zw = [&]() {
+            if (kEpi && Q.z) load_pair(static_cast<const SpT<R> *>(Q.z), P.S, s, wave, zz);
+            if (kDot && Q.w && Q.w != Q.z) load_pair(static_cast<const SpT<R> *>(Q.w), P.S, s, wave, ww);
+        };
+        // the operands of the second part: in flight during the hops, or, where the registers do not hold them
+        // as well (FP64), from the end of the hop on
+        if (mine) {
+            if constexpr (kCanon) load_pair_canon(static_cast<const SpT<R> *>(Q.in), s, wave, acc);
+            else load_pair(static_cast<const SpT<R> *>(Q.in), P.S, s, wave, acc);
+            if constexpr (sizeof(R) == 4) load_zw();
+        }
+        {
+            cpx<R> chi[6];
+            switch (wave) {
+            case 0: split_hop<0, true, kCanon, R, LT>(P, Q, s, c[0], chi); break;
+            case 1: split_hop<0, false, kCanon, R, LT>(P, Q, s, c[0], chi); break;
+            case 2: split_hop<1, true, kCanon, R, LT>(P, Q, s, c[1], chi); break;
+            case 3: split_hop<1, false, kCanon, R, LT>(P, Q, s, c[1], chi); break;
+            case 4: split_hop<2, true, kCanon, R, LT>(P, Q, s, c[2], chi); break;
+            case 5: split_hop<2, false, kCanon, R, LT>(P, Q, s, c[2], chi); break;
+            case 6: split_hop<3, true, kCanon, R, LT>(P, Q, s, c[3], chi); break;
+            default: split_hop<3, false, kCanon, R, LT>(P, Q, s, c[3], chi); break;
+            }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) chi_lds[(wave * 6 + k) * kSplitSites + lane] = chi[k];
+            if (sizeof(R) == 8 && mine) load_zw();
+        }
+        __syncthreads();
+        double dr = 0.0, di = 0.0, dn = 0.0;
+        if (mine) {
+            const cpx<R> *chi = chi_lds + lane;
+            switch (wave) {
+            case 0: split_sum<0, R>(acc, P, Q, c, chi); break;
+            case 1: split_sum<1, R>(acc, P, Q, c, chi); break;
+            case 2: split_sum<2, R>(acc, P, Q, c, chi); break;
+            case 3: split_sum<3, R>(acc, P, Q, c, chi); break;
+            case 4: split_sum<4, R>(acc, P, Q, c, chi); break;
+            default: split_sum<5, R>(acc, P, Q, c, chi); break;
+            }
+            // gamma5 of the result (components 6..11) and the epilogue, as in finish_site
+            const R s5o = wave < 3 ? R(1) : static_cast<R>(Q.s5_out);
+            if constexpr (!kEpi) {
+                acc[0] = s5o * acc[0];
+                acc[1] = s5o * acc[1];
+            } else {
+                if (Q.in_scale) {
+                    const z64 t = *Q.in_scale;
+                    const cpx<R> sc = {static_cast<R>(Q.a * t.r), static_cast<R>(Q.a * t.i)};
+                    const cpx<R> sl = {s5o * sc.r, s5o * sc.i};
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) acc[k] = cmul_f<false>(sl, acc[k]);
+                } else {
+                    const R a = s5o * static_cast<R>(Q.a);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) acc[k] = a * acc[k];
+                }
+                if (Q.z) {
+                    if (!Q.b_dev && Q.b.i == 0.0) {
+                        const R b = static_cast<R>(Q.b.r);
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) acc[k] = add_ph<kP1>(acc[k], b, zz[k]);
+                    } else {
+                        z64 bb = Q.b;
+                        if (Q.b_dev) {
+                            const z64 t = *Q.b_dev;
+                            bb = {bb.r * t.r - bb.i * t.i, bb.r * t.i + bb.i * t.r};
+                        }
+                        const cpx<R> b = {static_cast<R>(bb.r), static_cast<R>(bb.i)};
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) cmac_f<false>(acc[k], b, zz[k]);
+                    }
+                }
+            }
+            if constexpr (kCanon) {
+                out_lds[lane * 13 + 2 * wave] = acc[0];
+                out_lds[lane * 13 + 2 * wave + 1] = acc[1];
+            } else if (valid) {
+                store_pair(static_cast<SpT<R> *>(Q.out), P.S, s, wave, acc);
+            }
+            if constexpr (kDot) {
+                if (Q.w && valid) {
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const z64 a = cast<double>(Q.w == Q.z ? zz[k] : ww[k]), o = cast<double>(acc[k]);
+                        dr += a.r * o.r + a.i * o.i;
+                        di += a.r * o.i - a.i * o.r;
+                        dn += o.r * o.r + o.i * o.i;
+                    }
+                }
+            }
+        }
+        if constexpr (kCanon) {
+            // the block's sites are one contiguous piece of the canonical output: written in order
+            __syncthreads();
+            const int n = min(kSplitSites, P.V - s0) * 12;
+            SGN_GLOBAL cpx<R> *o = (SGN_GLOBAL cpx<R> *)Q.out + (size_t)s0 * 12;
+            for (int e = threadIdx.x; e < n; e += kSplitThreads) o[e] = out_lds[e / 12 * 13 + e % 12];
+        }
+        if constexpr (kDot) {
+            __shared__ double red[3 * (kSplitThreads / 64)];
+            if (Q.w) {  // uniform
+                double v[3] = {dr, di, dn};
+                block_sum<3>(v, red);
+                if (threadIdx.x == 0) {
+                    if (Q.norm) {
+                        Q.partials[2 * bx] = {v[0], v[1]};
+                        Q.partials[2 * bx + 1] = {v[2], 0.0};
+                    } else {
+                        Q.partials[bx] = {v[0], v[1]};
+                    }
+                }
+            }
+        }
+    }
+}
+
+// (four waves per SIMD, i.e. two blocks per CU, for FP64 too: 128 VGPRs instead of 126-148)
+template <typename R, typename LT, bool kEpi, bool kDot, bool kCanon>
+__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4))) stencil_split_kernel(StencilParams P)
+{
+    split_body<R, LT, kEpi, kDot, kCanon, false>(P, (int)blockIdx.x);
+}
+
+template <typename R, typename LT, bool kEpi, bool kDot>
+__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4))) stencil_split_batch(const StencilParams *__restrict__ plist)
+{
+    const StencilParams &P = plist[blockIdx.y];
+    if ((int)blockIdx.x >= P.nblk_total) return;
+    split_body<R, LT, kEpi, kDot, false, true>(P, (int)blockIdx.x);
+}
+
+template <typename R, typename LT>
+void launch_split(const StencilParams &P, int nblk, bool epi, bool dot, bool canon, hipStream_t s,
+                  const LaunchStamp &ev)
+{
+    dim3 g(nblk), b(kSplitThreads);
+    if (canon)  // no padding sites in the canonical layout
+        launch_k(ev, stencil_split_kernel<R, LT, false, false, true>, dim3(P.nblk_sites), b, 0u, s, P);
+    else if (dot)
+        launch_k(ev, stencil_split_kernel<R, LT, true, true, false>, g, b, 0u, s, P);
+    else if (epi)
+        launch_k(ev, stencil_split_kernel<R, LT, true, false, false>, g, b, 0u, s, P);
+    else
+        launch_k(ev, stencil_split_kernel<R, LT, false, false, false>, g, b, 0u, s, P);
+}
+
 template <typename R, typename LT>
 void launch_staged(const StencilParams &P, int nblk, int threads, size_t lds, bool epi, bool dot, hipStream_t s,
                    const LaunchStamp &ev)
@@ -823,10 +1235,30 @@ int dslash_blocks(const Lattice &lat)
 
 namespace {
 
+// Internal fields up to this size take the split kernel unless a staged shape was tuned or pinned for their
+// lattice (49152 FP64 or 98304 FP32 sites): beyond it the chip is full either way and the staged kernel's
+// reuse of neighbours wins.  One application, split against the best staged shape: 4^4 FP64 4.1 / 6.7 us,
+// 8^4 4.6 / 7.6, 12^4 7.5 / 9.8, 40320 sites 10.0 / 11.0, 16^4 15.1 / 14.5; FP32 8^4 3.9 / 6.8, 16^4
+// 8.4 / 9.3, 70200 sites 9.4 / 10.3, 16^3 x 32 14.0 / 12.5.
+constexpr int64_t kSplitMaxBytes = 9 << 20;
+
+bool split_fits(const Lattice &lat, sgn_prec p)
+{
+    return lat.V * (p == SGN_PREC_F64 ? 192 : 96) <= kSplitMaxBytes;
+}
+
+bool use_split(const Lattice &lat, sgn_prec p, bool multi)
+{
+    if (!split_fits(lat, p)) return false;
+    auto it = lat.ctx->tuned.find({lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, multi ? 1 : 0});
+    return it == lat.ctx->tuned.end() || it->second.unstaged;
+}
+
 // Everything about one stencil application except the launch itself.
 struct PreparedStencil {
     StencilParams P{};
     StagedPlan pl;
+    bool split = false;  // the split kernel (pl is then not used)
     int nblk = 0;       // blocks of the launch (= partials written when dotting)
     double bytes = 0.0;         // algorithmic bytes (links as nine entries) and flops
     double flops = 0.0;
@@ -836,7 +1268,7 @@ struct PreparedStencil {
 
 // max_threads > 0 caps the staged block (the register-link multi-RHS form)
 PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
-                                void *const *out, const Epilogue *ep, int max_threads = 0)
+                                void *const *out, const Epilogue *ep, int max_threads = 0, bool canon = false)
 {
     if (nr < 1 || nr > kMaxRhs) throw Failure{SGN_ERR_INVALID, "stencil: 1..16 right-hand sides per launch"};
     PreparedStencil ps;
@@ -902,7 +1334,17 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
     ps.flops = (1368.0 * nr + extra_flops) * lat.V;
     P.nrhs = nr;
     P.tslices = 1;
-    {
+    ps.split = canon || use_split(lat, p, nr > 1);
+    if (ps.split) {
+        P.sched_T = P.sched_R = 0;
+        const int64_t v3 = (int64_t)lat.L[0] * lat.L[1] * lat.L[2];
+        if (v3 % kSplitSites == 0 && lat.L[3] % 8 == 0) {
+            P.sched_T = lat.L[3] / 8;
+            P.sched_R = (int)(v3 / kSplitSites);
+        }
+        P.nblk_sites = (int)((lat.V + kSplitSites - 1) / kSplitSites);
+        ps.nblk = P.nblk_sites + (int)((lat.S - lat.V + kSplitThreads - 1) / kSplitThreads);
+    } else {
         const Context::TunedShape ts = lat.ctx->tuned_shape(lat.L, p, nr > 1);
         if (!ts.unstaged) {
             ps.pl = staged_plan(lat, p, max_threads, ts.max_sites, ts.tslices);
@@ -923,7 +1365,7 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
         }
     }
     P.nblk_total = ps.nblk;
-    if (lat.gauge && ps.pl.ok) {  // the staged kernel reads the time links of the last slice only
+    if (lat.gauge && (ps.pl.ok || ps.split)) {  // these kernels read the time links of the last slice only
         P.tgauge = 1;
         ps.bytes_stored -= (1.0 - 1.0 / lat.L[3]) * lat.link_ne * ((p == SGN_PREC_F64) ? 16.0 : (p == SGN_PREC_F32 ? 8.0 : 4.0)) * lat.V;
     }
@@ -959,6 +1401,19 @@ void launch_staged_batch_r(const StencilParams *dev, int count, int gx, int thre
 }
 
 template <typename R, typename LT>
+void launch_split_batch(const StencilParams *dev, int count, int gx, bool epi, bool dot, hipStream_t s,
+                        const LaunchStamp &ev)
+{
+    dim3 g(gx, count), b(kSplitThreads);
+    if (dot)
+        launch_k(ev, stencil_split_batch<R, LT, true, true>, g, b, 0u, s, dev);
+    else if (epi)
+        launch_k(ev, stencil_split_batch<R, LT, true, false>, g, b, 0u, s, dev);
+    else
+        launch_k(ev, stencil_split_batch<R, LT, false, false>, g, b, 0u, s, dev);
+}
+
+template <typename R, typename LT>
 void launch_staged_batch(const StencilParams *dev, int count, int gx, int threads, size_t lds, bool epi, bool dot,
                          bool regs, hipStream_t s, const LaunchStamp &ev)
 {
@@ -973,11 +1428,14 @@ void launch_staged_batch(const StencilParams *dev, int count, int gx, int thread
 
 }  // namespace
 
-int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
-                        void *const *out, const Epilogue *ep, hipStream_t s)
+namespace {
+
+// canon: one right-hand side without an epilogue, in and out in the canonical layout (split kernel only)
+int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in, void *const *out,
+                 const Epilogue *ep, hipStream_t s, bool canon)
 {
-    const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep);
-    if (nr > 1 && ps.pl.ok) {
+    const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep, 0, canon);
+    if (nr > 1 && (ps.pl.ok || ps.split)) {
         // several right-hand sides: the batched form, one group, parameters in device memory
         // (the lattice's batch object: they are uploaded when they change, after the device has
         // finished the launches that read the previous ones)
@@ -993,19 +1451,25 @@ int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op
     const LaunchStamp ev = lat.ctx->prof_stamp(prof);
     switch (p) {
     case SGN_PREC_F64:
-        if (ps.pl.ok)
+        if (ps.split)
+            launch_split<double, double2>(ps.P, ps.nblk, ps.epi, ps.dot, canon, s, ev);
+        else if (ps.pl.ok)
             launch_staged<double, double2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, ps.epi, ps.dot, s, ev);
         else
             launch_nr<double, double2>(ps.P, nr, ps.nblk, ps.epi, ps.dot, s, ev);
         break;
     case SGN_PREC_F32:
-        if (ps.pl.ok)
+        if (ps.split)
+            launch_split<float, float2>(ps.P, ps.nblk, ps.epi, ps.dot, canon, s, ev);
+        else if (ps.pl.ok)
             launch_staged<float, float2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, ps.epi, ps.dot, s, ev);
         else
             launch_nr<float, float2>(ps.P, nr, ps.nblk, ps.epi, ps.dot, s, ev);
         break;
     default:
-        if (ps.pl.ok)
+        if (ps.split)
+            launch_split<float, __half2>(ps.P, ps.nblk, ps.epi, ps.dot, canon, s, ev);
+        else if (ps.pl.ok)
             launch_staged<float, __half2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, ps.epi, ps.dot, s, ev);
         else
             launch_nr<float, __half2>(ps.P, nr, ps.nblk, ps.epi, ps.dot, s, ev);
@@ -1014,6 +1478,24 @@ int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op
     SGN_HIP(hipGetLastError());
     lat.ctx->prof_stop(prof, s, kclass(p), ps.bytes, ps.flops, false, ps.bytes_stored);
     return ps.nblk;
+}
+
+}  // namespace
+
+int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
+                        void *const *out, const Epilogue *ep, hipStream_t s)
+{
+    return launch_multi(lat, p, nr, op, in, out, ep, s, false);
+}
+
+bool dslash_launch_canon(const Lattice &lat, sgn_prec p, const OpSpec &op, const void *in, void *out, hipStream_t s)
+{
+    const size_t bytes = (size_t)lat.V * (p == SGN_PREC_F64 ? 192 : 96);
+    const uintptr_t a = reinterpret_cast<uintptr_t>(in), b = reinterpret_cast<uintptr_t>(out);
+    if (lat.gauge || (a | b) % 16 != 0 || (a < b + bytes && b < a + bytes)) return false;
+    const Epilogue ep;
+    launch_multi(lat, p, 1, &op, &in, &out, &ep, s, true);
+    return true;
 }
 
 StencilBatch::~StencilBatch()
@@ -1048,7 +1530,9 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
                 cnt.push_back(0);
                 const Context::TunedShape ts = j.lat->ctx->tuned_shape(j.lat->L, p, true);
                 const StagedPlan pl = staged_plan(*j.lat, p, 0, ts.max_sites, ts.tslices);
-                per.push_back(pl.ok ? pl.nblk_sites : (j.lat->V + 255) / 256);
+                per.push_back(use_split(*j.lat, p, true) ? (j.lat->V + kSplitSites - 1) / kSplitSites
+                              : pl.ok                    ? pl.nblk_sites
+                                                         : (j.lat->V + 255) / 256);
             }
             ++cnt[l];
         }
@@ -1068,17 +1552,25 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
         if (g == groups.size()) groups.emplace_back();
         groups[g].push_back(k);
     }
+    // the groups of small lattices first: they are the split kernel's launch, the others the staged kernel's
+    nsplit_ = (int)(std::stable_partition(groups.begin(), groups.end(),
+                                          [&](const std::vector<size_t> &g) {
+                                              return use_split(*jobs[g[0]].lat, p, g.size() > 1);
+                                          }) -
+                    groups.begin());
+    gx_split_ = 0;
     // links in registers (FP16 two-row links, some group with several right-hand sides, and the
     // environment does not ask for re-reads: SGN_MULTI_LINK_REGS=0)
     regs_ = p == SGN_PREC_F32_H16;
     bool multi = false;
-    for (size_t g = 0; g < groups.size(); ++g) {
+    for (size_t g = nsplit_; g < groups.size(); ++g) {
         multi = multi || groups[g].size() > 1;
         regs_ = regs_ && jobs[groups[g][0]].lat->link_ne == 6;
     }
     {
         const char *e = std::getenv("SGN_MULTI_LINK_REGS");
-        const int tuned = groups.empty() ? -1 : jobs[groups[0][0]].lat->ctx->tuned_shape(jobs[groups[0][0]].lat->L, p, true).regs;
+        const Lattice *l0 = (size_t)nsplit_ < groups.size() ? jobs[groups[nsplit_][0]].lat : nullptr;
+        const int tuned = l0 ? l0->ctx->tuned_shape(l0->L, p, true).regs : -1;
         regs_ = regs_ && multi && !(e && e[0] == '0') && tuned != 0;
     }
     std::vector<StencilParams> host(groups.size());
@@ -1100,18 +1592,23 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
                                                    regs_ ? kRegsMaxThreads : 0);
         host[g] = ps.P;
         for (size_t k : groups[g]) nblk_[k] = ps.nblk;
-        batched_ = batched_ && ps.pl.ok;
+        batched_ = batched_ && (ps.pl.ok || ps.split);
         epi_ = epi_ || ps.epi;
         dot_ = dot_ || ps.dot;
-        gx_ = std::max(gx_, ps.nblk);
-        threads_ = std::max(threads_, ps.pl.threads);
-        lds_ = std::max(lds_, ps.pl.lds);
+        if (ps.split) {
+            gx_split_ = std::max(gx_split_, ps.nblk);
+        } else {
+            gx_ = std::max(gx_, ps.nblk);
+            threads_ = std::max(threads_, ps.pl.threads);
+            lds_ = std::max(lds_, ps.pl.lds);
+        }
         bytes_ += ps.bytes;
         bytes_stored_ += ps.bytes_stored;
         flops_ += ps.flops;
     }
-    ngroups_ = (int)groups.size();
+    ngroups_ = (int)groups.size() - nsplit_;
     gx_ = (gx_ + 7) / 8 * 8;
+    gx_split_ = (gx_split_ + 7) / 8 * 8;
     if (!batched_) return;
     const size_t need = sizeof(StencilParams) * host.size();
     // unchanged parameters stay on the device; new ones wait until no launch reads the old
@@ -1136,18 +1633,27 @@ void StencilBatch::launch(hipStream_t s) const
         return;
     }
     Context *ctx = jobs_[0].lat->ctx;
-    const int prof = ctx->prof_start(s, kclass(prec_), true);
+    const int prof = ctx->prof_start(s, kclass(prec_), !nsplit_ || !ngroups_);  // a stamp takes one kernel
     const LaunchStamp ev = ctx->prof_stamp(prof);
     const StencilParams *d = static_cast<const StencilParams *>(dev_);
-    const int cnt = ngroups_;
-    switch (prec_) {
-    case SGN_PREC_F64:
-        launch_staged_batch<double, double2>(d, cnt, gx_, threads_, lds_, epi_, dot_, false, s, ev);
-        break;
-    case SGN_PREC_F32:
-        launch_staged_batch<float, float2>(d, cnt, gx_, threads_, lds_, epi_, dot_, regs_, s, ev);
-        break;
-    default: launch_staged_batch<float, __half2>(d, cnt, gx_, threads_, lds_, epi_, dot_, regs_, s, ev); break;
+    if (nsplit_) {
+        switch (prec_) {
+        case SGN_PREC_F64: launch_split_batch<double, double2>(d, nsplit_, gx_split_, epi_, dot_, s, ev); break;
+        case SGN_PREC_F32: launch_split_batch<float, float2>(d, nsplit_, gx_split_, epi_, dot_, s, ev); break;
+        default: launch_split_batch<float, __half2>(d, nsplit_, gx_split_, epi_, dot_, s, ev); break;
+        }
+    }
+    if (ngroups_) {
+        d += nsplit_;
+        switch (prec_) {
+        case SGN_PREC_F64:
+            launch_staged_batch<double, double2>(d, ngroups_, gx_, threads_, lds_, epi_, dot_, false, s, ev);
+            break;
+        case SGN_PREC_F32:
+            launch_staged_batch<float, float2>(d, ngroups_, gx_, threads_, lds_, epi_, dot_, regs_, s, ev);
+            break;
+        default: launch_staged_batch<float, __half2>(d, ngroups_, gx_, threads_, lds_, epi_, dot_, regs_, s, ev); break;
+        }
     }
     SGN_HIP(hipGetLastError());
     ctx->prof_stop(prof, s, kclass(prec_), bytes_, flops_, false, bytes_stored_);
@@ -1222,6 +1728,7 @@ static sgn_status apply_common(sgn_lattice l, double mu, const void *in, void *o
         if (flags & SGN_INTERNAL_LAYOUT) {
             dslash_launch(lat, p, op, in, out, ep, s);
         } else {
+            if (dslash_launch_canon(lat, p, op, in, out, s)) return;
             const size_t bytes = spinor_bytes(lat.S, p);
             lat.ensure_stage(bytes);
             pack_spinor(lat, in, lat.stage_in, p, s);
@@ -1270,6 +1777,7 @@ extern "C" sgn_status wilson_apply_noalloc(sgn_lattice l, double mu, const void 
                                                " staging bytes, more than SGN_NOALLOC_MAX_BYTES = " +
                                                std::to_string((size_t)SGN_NOALLOC_MAX_BYTES)};
         SGN_REQUIRE(lat.ctx->noalloc != nullptr, "wilson_apply_noalloc: scratch address not set up");
+        if (dslash_launch_canon(lat, p, op, in, out, s)) return;
         char *stage_in = static_cast<char *>(lat.ctx->noalloc);
         char *stage_out = stage_in + off;
         pack_spinor(lat, in, stage_in, p, s);
@@ -1302,7 +1810,8 @@ extern "C" sgn_status sgn_autotune(sgn_lattice l, sgn_prec p, int nrhs, int reps
             int unstaged;
         };
         std::vector<Cand> cands;
-        if (!multi) cands.push_back({0, 0, 1, -1, 0.0, 1});  // the unstaged kernel
+        // the unstaged kernel, or on small lattices the split one (also for several right-hand sides)
+        if (!multi || split_fits(lat, p)) cands.push_back({0, 0, 1, -1, 0.0, 1});
         const bool can_regs = multi && p == SGN_PREC_F32_H16 && lat.link_ne == 6;
         for (int regs : can_regs ? std::vector<int>{1, 0} : std::vector<int>{-1}) {
             for (int T : {1, 2}) {

@@ -228,6 +228,9 @@ int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op
                         void *const *out, const Epilogue *ep, hipStream_t s);
 int dslash_launch(const Lattice &lat, sgn_prec p, const OpSpec &op, const void *in, void *out,
                   const Epilogue &ep, hipStream_t s);
+// The operator on canonical-layout fields in one launch, where a kernel takes them; false (nothing
+// launched) where the caller has to go through the internal layout.
+bool dslash_launch_canon(const Lattice &lat, sgn_prec p, const OpSpec &op, const void *in, void *out, hipStream_t s);
 int dslash_blocks(const Lattice &lat);
 
 // One single-RHS stencil application of a batch.
@@ -263,7 +266,8 @@ class StencilBatch {
     void *dev_ = nullptr;
     size_t dev_bytes_ = 0;
     std::vector<char> uploaded_;  // the parameters now on the device
-    int gx_ = 0, threads_ = 0, ngroups_ = 0;
+    int gx_ = 0, threads_ = 0, ngroups_ = 0;   // of the staged kernel's groups
+    int gx_split_ = 0, nsplit_ = 0;            // of the split kernel's, which come first in dev_
     size_t lds_ = 0;
     bool batched_ = false, epi_ = false, dot_ = false, regs_ = false;
     double bytes_ = 0.0, flops_ = 0.0, bytes_stored_ = 0.0;

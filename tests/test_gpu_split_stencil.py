@@ -1,0 +1,60 @@
+"""The split stencil (eight wavefronts per 64 sites) and its canonical-layout form: the same operator, bit for
+bit, as the staged kernel, at the edges of its blocks of 64 sites and of its size range."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import WilsonRef
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_0910_1048_amd as sgn  # noqa: E402
+from gpu_util import ctx, dev, host  # noqa: E402
+
+CDT = {sgn.F64: np.complex128, sgn.F32: np.complex64, sgn.F32_H16: np.complex64}
+TOL = {sgn.F64: 1e-13, sgn.F32: 1e-6, sgn.F32_H16: 5e-3}
+# 16 and 48 sites (no full block), 63 and 65 around one block, a remainder of 4 lanes in the last block,
+# padded component arrays, and the last sizes on either side of the FP64 and FP32 limits
+DIMS = [(2, 2, 2, 2), (2, 2, 2, 6), (3, 3, 7, 1 + 1), (5, 13, 2, 2), (4, 4, 4, 4), (5, 7, 3, 4), (8, 8, 8, 8),
+        (16, 16, 16, 12), (16, 16, 8, 25), (16, 16, 16, 24), (16, 16, 24, 17)]
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32, sgn.F32_H16])
+@pytest.mark.parametrize("dims", DIMS)
+@pytest.mark.parametrize("flags", [0, sgn.LINKS_FULL, sgn.LINKS_TEMPORAL_GAUGE])
+def test_split_and_canonical_forms_are_the_same_operator(dims, prec, flags):
+    U = synth.gauge_field(dims, 0.4, 7)
+    W = WilsonRef(U, dims, 0.2)
+    lat = sgn.Lattice(ctx(), dev(U), dims, 0.2, prec_mask=flags)
+    b = synth.gaussian_source(dims, 3).astype(CDT[prec])
+    bd = dev(b)
+    nb = lat.spinor_bytes(prec)
+    xi, yi = (torch.empty(nb, dtype=torch.uint8, device="cuda") for _ in range(2))
+    sgn.sgn_spinor_pack(lat, bd, xi, prec)
+
+    def results():
+        canon, dag, plain, back = (torch.empty_like(bd) for _ in range(4))
+        sgn.wilson_apply(lat, 0.2, bd, canon, prec)
+        sgn.wilson_apply_dag(lat, 0.2, bd, dag, prec)
+        sgn.wilson_apply_dag(lat, 0.2, bd, plain, prec, sgn.NO_GAMMA5)
+        yi.fill_(0x5A)   # the padding sites have to be written too
+        sgn.wilson_apply(lat, 0.2, xi, yi, prec, sgn.INTERNAL_LAYOUT)
+        multi = [torch.empty_like(yi) for _ in range(3)]
+        sgn.wilson_apply_multi(lat, [0.2, -0.1, 0.2], [xi, xi, xi], multi, prec)
+        sgn.sgn_spinor_unpack(lat, yi, back, prec)
+        return [canon, dag, plain, yi.clone(), multi[0], multi[1], multi[2], back]
+
+    first = results()
+    ref = b.astype(np.complex128)
+    for got, want in zip(first, (W.apply(ref, 0.2), W.apply_adj(ref, 0.2), W.apply_adj(ref, 0.2, g5=False))):
+        err = np.linalg.norm(host(got) - want) / np.linalg.norm(want)
+        assert err < TOL[prec], err
+    assert torch.equal(first[0], first[7]) and torch.equal(first[3], first[4]) and torch.equal(first[4], first[6])
+    try:
+        sgn.sgn_tune_set(lat, prec, False, 0, 1)   # the staged kernel from here on
+        sgn.sgn_tune_set(lat, prec, True, 0, 1)
+    except sgn.SgnError:
+        return                                     # no staged block fits so small a lattice
+    for a, c in zip(first, results()):
+        assert torch.equal(a, c)
