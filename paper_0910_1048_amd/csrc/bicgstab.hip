@@ -517,12 +517,19 @@ __device__ __forceinline__ void stz_nt(float2 *p, int64_t e, z64 v)
     __builtin_nontemporal_store(nt_f2{(float)v.r, (float)v.i}, (SGN_GLOBAL nt_f2 *)p + e);
 }
 
-// alpha = rho / r^^H v from the dotting stencil's partials; the BiCG factors zeta_next
-// The one-block scalar steps are bound by memory latency: each issues all its loads (the flags,
-// the partials and, in the thread of each shift, that shift's state) before the first use.
+// alpha and omega come in two forms.  With few partial sums (small lattices) every block of the vector kernel
+// that needs the scalar adds the partials itself, in one order, and its block 0 writes the state: two launches
+// fewer per iteration (8^4 FP64: s and r' updates with their scalars 13.0 -> 9.5 us, and two gaps less).  Above
+// kBsFusedPartials the re-reads cost more than a launch and one block does it alone.  beta keeps its own
+// launch (5.7 us): its code is long, and fetched by every CU it made the 3.4 us x, p update take 17 us.
+// All of them are bound by latency: the loads (the flags, the partials and, in the thread of each shift, that
+// shift's state) are issued before the first use.
+constexpr int kBsFusedPartials = 1024;
 static_assert(kBsShifts <= 256, "one thread per shift in the 256-thread scalar kernels");
 
-__device__ __forceinline__ void bs_alpha_kernel_body(BsState *S, const z64 *part, int nb)
+// alpha = rho / r^^H v from the dotting stencil's partials; the BiCG factors zeta_next (writer: this block
+// updates the state).  False if the iteration is over (done, or a breakdown); otherwise alpha in al.
+__device__ __forceinline__ bool bs_alpha_body(BsState *S, const z64 *part, int nb, bool writer, z64 &al)
 {
     const int done = S->h.done, ns = S->h.ns, i = threadIdx.x;
     const z64 rho = S->h.rho, ap = S->h.alpha_prev, bp = S->h.beta_prev;
@@ -534,13 +541,12 @@ __device__ __forceinline__ void bs_alpha_kernel_body(BsState *S, const z64 *part
     int act = 0;
     z64 z = {0.0, 0.0}, zp = {0.0, 0.0};
     double tau = 0.0;
-    if (i < ns) {
+    if (writer && i < ns) {
         act = S->act[i];
         z = S->zeta[i];
         zp = S->zeta_prev[i];
         tau = S->tau[i];
     }
-    if (done) return;
     __shared__ double lds[8];
     __shared__ int bad;
     __shared__ z64 al_sh;
@@ -549,39 +555,47 @@ __device__ __forceinline__ void bs_alpha_kernel_body(BsState *S, const z64 *part
     if (i == 0) {
         const z64 den = {v[0], v[1]};
         z64 a = bs_div(rho, den);
-        bad = 0;
-        if (!(den.r * den.r + den.i * den.i > 0.0) || !bs_finite(a)) {
-            S->h.breakdown = 1;
-            S->h.done = 1;
+        bad = done;  // one thread's reading decides for the block: block 0 may set the flag meanwhile
+        if (!done && (!(den.r * den.r + den.i * den.i > 0.0) || !bs_finite(a))) {
+            if (writer) {
+                S->h.breakdown = 1;
+                S->h.done = 1;
+            }
             a = {0.0, 0.0};
             bad = 1;
         }
-        S->h.alpha = a;
+        if (writer && !done) S->h.alpha = a;
         al_sh = a;
     }
     __syncthreads();
-    if (bad || i >= ns) return;
-    if (!act) {
-        S->zeta_next[i] = z;
-        return;
+    if (bad) return false;
+    al = al_sh;
+    if (writer && i < ns) {
+        const z64 one_tau = {1.0 + tau * al.r, tau * al.i};
+        S->zeta_next[i] = act ? bs_div(z * zp * ap, ap * one_tau * zp + al * bp * (zp - z)) : z;
     }
-    const z64 al = al_sh;
-    const z64 one_tau = {1.0 + tau * al.r, tau * al.i};
-    S->zeta_next[i] = bs_div(z * zp * ap, ap * one_tau * zp + al * bp * (zp - z));
+    return true;
 }
 __global__ void __launch_bounds__(256) bs_alpha_kernel(BsState *S, const z64 *part, int nb)
 {
-    bs_alpha_kernel_body(S, part, nb);
+    z64 al;
+    bs_alpha_body(S, part, nb, true, al);
 }
 
 // s = r_k - alpha v (r_k read from its slot), into the work vector and the slot of iteration k
+// (nb > 0: alpha is taken from the nb partials here)
 template <typename R>
-__device__ __forceinline__ void bs_sub_stored_body(const BsState *S, void *const *rslots, const typename BsVec<R>::t *v,
-                              typename BsVec<R>::t *s, void *const *sslots, int64_t n)
+__device__ __forceinline__ void bs_sub_stored_body(BsState *S, const z64 *part, int nb, void *const *rslots,
+                              const typename BsVec<R>::t *v, typename BsVec<R>::t *s, void *const *sslots, int64_t n)
 {
     using T = typename BsVec<R>::t;
-    if (S->h.done) return;
-    const z64 al = S->h.alpha;
+    z64 al;
+    if (nb > 0) {
+        if (!bs_alpha_body(S, part, nb, blockIdx.x == 0, al)) return;
+    } else {
+        if (S->h.done) return;
+        al = S->h.alpha;
+    }
     const T *r = static_cast<const T *>(rslots[S->h.iter]);
     T *slot = static_cast<T *>(sslots[S->h.iter]);
     // r_k is next read by the lift, v only after two stencils: non-temporal reads keep them from
@@ -593,43 +607,58 @@ __device__ __forceinline__ void bs_sub_stored_body(const BsState *S, void *const
     }
 }
 template <typename R>
-__global__ void __launch_bounds__(256) bs_sub_stored(const BsState *S, void *const *rslots, const typename BsVec<R>::t *v,
-                              typename BsVec<R>::t *s, void *const *sslots, int64_t n)
+__global__ void __launch_bounds__(256) bs_sub_stored(BsState *S, const z64 *part, int nb, void *const *rslots,
+                              const typename BsVec<R>::t *v, typename BsVec<R>::t *s, void *const *sslots, int64_t n)
 {
-    bs_sub_stored_body<R>(S, rslots, v, s, sslots, n);
+    bs_sub_stored_body<R>(S, part, nb, rslots, v, s, sslots, n);
 }
 
 // omega = t^H s / t^H t (0 when t = 0: s was the exact residual 0), from the partials
 // {s^H t, ||t||^2} per block of the stencil that produced t
-__device__ __forceinline__ void bs_omega_kernel_body(BsState *S, const z64 *part, int nb)
+__device__ __forceinline__ bool bs_omega_body(BsState *S, const z64 *part, int nb, bool writer, z64 &om)
 {
-    const int done = S->h.done;
+    const int done = S->h.done;  // not written by the kernels this runs in
     double a = 0.0, b = 0.0, c = 0.0;
     for (int i = threadIdx.x; i < nb; i += blockDim.x) {
         a += part[2 * i].r;
         b += part[2 * i].i;
         c += part[2 * i + 1].r;
     }
-    if (done) return;
+    if (done) return false;
     __shared__ double lds[12];
+    __shared__ z64 om_sh;
     double v[3] = {a, b, c};
     block_sum<3>(v, lds);
-    if (threadIdx.x == 0) S->h.omega = v[2] > 0.0 ? z64{v[0] / v[2], -v[1] / v[2]} : z64{0.0, 0.0};
+    if (threadIdx.x == 0) {
+        om_sh = v[2] > 0.0 ? z64{v[0] / v[2], -v[1] / v[2]} : z64{0.0, 0.0};
+        if (writer) S->h.omega = om_sh;
+    }
+    __syncthreads();
+    om = om_sh;
+    return true;
 }
 __global__ void __launch_bounds__(256) bs_omega_kernel(BsState *S, const z64 *part, int nb)
 {
-    bs_omega_kernel_body(S, part, nb);
+    z64 om;
+    bs_omega_body(S, part, nb, true, om);
 }
 
 // r' = s - omega t into the slot of iteration k + 1 (the residual lives only there);
 // partials of r^^H r' and ||r'||^2 (of the stored values)
+// (nb > 0: omega is taken from the nb partials of opart here)
 template <typename R>
-__device__ __forceinline__ void bs_res_stored_body(const BsState *S, const typename BsVec<R>::t *s, const typename BsVec<R>::t *t,
-                              const typename BsVec<R>::t *rh, void *const *rslots, int64_t n, z64 *part)
+__device__ __forceinline__ void bs_res_stored_body(BsState *S, const z64 *opart, int nb, const typename BsVec<R>::t *s,
+                              const typename BsVec<R>::t *t, const typename BsVec<R>::t *rh, void *const *rslots,
+                              int64_t n, z64 *part)
 {
     using T = typename BsVec<R>::t;
-    if (S->h.done) return;
-    const z64 om = S->h.omega;
+    z64 om;
+    if (nb > 0) {
+        if (!bs_omega_body(S, opart, nb, blockIdx.x == 0, om)) return;
+    } else {
+        if (S->h.done) return;
+        om = S->h.omega;
+    }
     T *r = static_cast<T *>(rslots[S->h.iter + 1]);
     double a = 0.0, b = 0.0, c = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
@@ -650,10 +679,11 @@ __device__ __forceinline__ void bs_res_stored_body(const BsState *S, const typen
     }
 }
 template <typename R>
-__global__ void __launch_bounds__(256) bs_res_stored(const BsState *S, const typename BsVec<R>::t *s, const typename BsVec<R>::t *t,
-                              const typename BsVec<R>::t *rh, void *const *rslots, int64_t n, z64 *part)
+__global__ void __launch_bounds__(256) bs_res_stored(BsState *S, const z64 *opart, int nb, const typename BsVec<R>::t *s,
+                              const typename BsVec<R>::t *t, const typename BsVec<R>::t *rh, void *const *rslots,
+                              int64_t n, z64 *part)
 {
-    bs_res_stored_body<R>(S, s, t, rh, rslots, n, part);
+    bs_res_stored_body<R>(S, opart, nb, s, t, rh, rslots, n, part);
 }
 
 // beta, the history entry, the shifted residual estimates and the control flags
@@ -912,7 +942,7 @@ struct BsDesc {
     void *const *stab;
     void *p, *v, *sv, *t, *rh;
     double2 *x64;
-    z64 *spart, *vpart;
+    z64 *spart, *vpart, *rpart;
     BsHist *hist;
     int64_t n;   // complex entries (12 S)
     int Sst;
@@ -924,32 +954,36 @@ struct BsDesc {
 __global__ void __launch_bounds__(256) bs_alpha_batch(const BsDesc *d)
 {
     const BsDesc &D = d[blockIdx.x];
-    bs_alpha_kernel_body(D.S, D.spart, D.nb_s);
+    z64 al;
+    bs_alpha_body(D.S, D.spart, D.nb_s, true, al);
 }
 __global__ void __launch_bounds__(256) bs_omega_batch(const BsDesc *d)
 {
     const BsDesc &D = d[blockIdx.x];
-    bs_omega_kernel_body(D.S, D.vpart, D.nb_v);
+    z64 om;
+    bs_omega_body(D.S, D.vpart, D.nb_v, true, om);
 }
 // nb: the grid width of the residual kernel that wrote the partials
 __global__ void __launch_bounds__(256) bs_beta_batch(const BsDesc *d, int nb)
 {
     const BsDesc &D = d[blockIdx.x];
-    bs_beta_kernel_body(D.S, D.vpart, nb, D.hist, D.cap);
+    bs_beta_kernel_body(D.S, D.rpart, nb, D.hist, D.cap);
 }
+// fused: the scalar step inside the vector kernel
 template <typename R>
-__global__ void __launch_bounds__(256) bs_sub_batch(const BsDesc *d)
+__global__ void __launch_bounds__(256) bs_sub_batch(const BsDesc *d, int fused)
 {
     using T = typename BsVec<R>::t;
     const BsDesc &D = d[blockIdx.y];
-    bs_sub_stored_body<R>(D.S, D.rtab, (const T *)D.v, (T *)D.sv, D.stab, D.n);
+    bs_sub_stored_body<R>(D.S, D.spart, fused ? D.nb_s : 0, D.rtab, (const T *)D.v, (T *)D.sv, D.stab, D.n);
 }
 template <typename R>
-__global__ void __launch_bounds__(256) bs_res_batch(const BsDesc *d)
+__global__ void __launch_bounds__(256) bs_res_batch(const BsDesc *d, int fused)
 {
     using T = typename BsVec<R>::t;
     const BsDesc &D = d[blockIdx.y];
-    bs_res_stored_body<R>(D.S, (const T *)D.sv, (const T *)D.t, (const T *)D.rh, D.rtab, D.n, D.vpart);
+    bs_res_stored_body<R>(D.S, D.vpart, fused ? D.nb_v : 0, (const T *)D.sv, (const T *)D.t, (const T *)D.rh, D.rtab,
+                          D.n, D.rpart);
 }
 __global__ void __launch_bounds__(256) bs_xp64_batch(const BsDesc *d)
 {
@@ -985,6 +1019,9 @@ struct BsSlotPools {
     std::map<size_t, size_t> next;  // next unused buffer of each per-size pool
     double budget = 0.0, used = 0.0;
 };
+
+constexpr int kBsSlotsAhead = 64;
+constexpr size_t kBsAheadBytes = 16 << 20;
 
 class BsStored {
     friend class BsBatch;
@@ -1029,7 +1066,7 @@ class BsStored {
     char *rh32_ = nullptr, *r32_ = nullptr, *s32_ = nullptr, *v32_ = nullptr, *t32_ = nullptr, *tmp32_ = nullptr,
          *p32_ = nullptr;
     char *rcan_ = nullptr;
-    z64 *spart_ = nullptr, *vpart_ = nullptr;
+    z64 *spart_ = nullptr, *vpart_ = nullptr, *rpart_ = nullptr;  // of the two dotting stencils and of r'
     BsState *S_ = nullptr;
     BsHist *hist_ = nullptr;
     void **rtab_ = nullptr, **stab_ = nullptr;  // device slot tables (r_k, s_k)
@@ -1084,13 +1121,26 @@ void *BsStored::take_slot(size_t bytes)
     return pool[next++];
 }
 
-// r-slots 0 .. upto + 1 and s-slots 0 .. upto; slots first written in the FP32 phase are FP32-sized
+// r-slots 0 .. upto + 1 and s-slots 0 .. upto; slots first written in the FP32 phase hold FP32 vectors.  Small
+// vectors: when the tables grow, slots for up to kBsSlotsAhead further iterations are taken along as far as the
+// pool has unused buffers (an FP32 vector may then sit in an FP64-sized one), since each growth costs two copies
+// that the stream waits for (with one growth per poll 1800 copies, 8 of 115 ms, in a batch of 24 problems).
 void BsStored::ensure_slots(int upto)
 {
     const size_t r0 = rslots_.size(), s0 = sslots_.size();
     const size_t bytes = lo() ? b32_ : b64_;
     while ((int)rslots_.size() < upto + 2) rslots_.push_back(take_slot(bytes));
     while ((int)sslots_.size() < upto + 1) sslots_.push_back(take_slot(bytes));
+    if (rslots_.size() == r0 && sslots_.size() == s0) return;
+    if (b64_ <= kBsAheadBytes && o_.basis_slots == 0) {
+        const size_t last = std::min<size_t>(maxiter_ + poll_, (size_t)upto + kBsSlotsAhead);
+        const std::vector<void *> &pool = ctx_.basis_pools[bytes];
+        while (rslots_.size() < last + 2 && sslots_.size() < last + 1 && pools_->next[bytes] + 2 <= pool.size() &&
+               pools_->used + 2.0 * (double)bytes <= 0.5 * pools_->budget) {
+            rslots_.push_back(take_slot(bytes));
+            sslots_.push_back(take_slot(bytes));
+        }
+    }
     if (rslots_.size() > r0)
         SGN_HIP(hipMemcpy(rtab_ + r0, rslots_.data() + r0, sizeof(void *) * (rslots_.size() - r0),
                           hipMemcpyHostToDevice));
@@ -1115,14 +1165,16 @@ void BsStored::launch_iteration(hipStream_t strm)
     e2.w = rh;
     e2.partials = spart_;
     const int nb = dslash_launch(lat_, sp, op, tmp, v, e2, strm);
-    hipLaunchKernelGGL(bs_alpha_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)spart_, nb);
+    const bool fused = nb <= kBsFusedPartials;  // both dotting stencils have the same blocks
+    if (!fused) hipLaunchKernelGGL(bs_alpha_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)spart_, nb);
+    const int nbs = fused ? nb : 0;
     const int pr = ctx_.prof_start(strm, SGN_K_SEED_UPDATE, true);
     if (f)
-        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<float>, dim3(nvb_), dim3(256), 0u, strm, (const BsState *)S_,
-                           (void *const *)rtab_, (const float2 *)v, (float2 *)sv, (void *const *)stab_, n_);
+        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<float>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)spart_, nbs, (void *const *)rtab_, (const float2 *)v, (float2 *)sv, (void *const *)stab_, n_);
     else
-        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<double>, dim3(nvb_), dim3(256), 0u, strm, (const BsState *)S_,
-                           (void *const *)rtab_, (const double2 *)v, (double2 *)sv, (void *const *)stab_, n_);
+        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<double>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)spart_, nbs, (void *const *)rtab_, (const double2 *)v, (double2 *)sv, (void *const *)stab_, n_);
     ctx_.prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * (f ? 8.0 : 16.0) * n_, 8.0 * n_);
     dslash_launch(lat_, sp, op, sv, tmp, Epilogue{}, strm);
     Epilogue e4;  // t = M s with the partials of s^H t and ||t||^2
@@ -1135,18 +1187,18 @@ void BsStored::launch_iteration(hipStream_t strm)
     const int nb4 = dslash_launch(lat_, sp, op, tmp, t, e4, strm);
     const double eb = f ? 8.0 : 16.0;
     int pr2 = -1;
-    hipLaunchKernelGGL(bs_omega_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)vpart_, nb4);
+    if (!fused) hipLaunchKernelGGL(bs_omega_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)vpart_, nb4);
     pr2 = ctx_.prof_start(strm, SGN_K_SEED_UPDATE, true);
     if (f)
-        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<float>, dim3(nvb_), dim3(256), 0u, strm, (const BsState *)S_,
-                           (const float2 *)sv, (const float2 *)t, (const float2 *)rh, (void *const *)rtab_, n_,
-                           vpart_);
+        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<float>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)vpart_, fused ? nb4 : 0, (const float2 *)sv, (const float2 *)t, (const float2 *)rh,
+                           (void *const *)rtab_, n_, rpart_);
     else
-        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<double>, dim3(nvb_), dim3(256), 0u, strm, (const BsState *)S_,
-                           (const double2 *)sv, (const double2 *)t, (const double2 *)rh, (void *const *)rtab_, n_,
-                           vpart_);
+        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<double>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)vpart_, fused ? nb4 : 0, (const double2 *)sv, (const double2 *)t, (const double2 *)rh,
+                           (void *const *)rtab_, n_, rpart_);
     ctx_.prof_stop(pr2, strm, SGN_K_SEED_UPDATE, 4.0 * eb * n_, 12.0 * n_);
-    hipLaunchKernelGGL(bs_beta_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)vpart_, nvb_, hist_, maxiter_);
+    hipLaunchKernelGGL(bs_beta_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)rpart_, nvb_, hist_, maxiter_);
     const int pr3 = ctx_.prof_start(strm, SGN_K_SHIFT_UPDATE, true);
     if (f)
         launch_k(ctx_.prof_stamp(pr3), bs_xp32, dim3(vec_blocks(6 * Sst_)), dim3(256), 0u, strm, (const BsState *)S_, (float4 *)p,
@@ -1347,7 +1399,7 @@ size_t BsStored::ws_bytes() const
 {
     const bool mixed = o_.prec != SGN_PREC_F64;
     const size_t nvp = 2 * (size_t)std::max(nst_, kMaxBlocks);
-    const size_t scal = sizeof(z64) * ((size_t)nst_ + nvp) + sizeof(BsState) + sizeof(BsHist) * (size_t)maxiter_ +
+    const size_t scal = sizeof(z64) * ((size_t)nst_ + nvp + 2 * (size_t)kMaxBlocks) + sizeof(BsState) + sizeof(BsHist) * (size_t)maxiter_ +
                         2 * sizeof(void *) * ((size_t)maxiter_ + poll_ + 4);
     return (8 * b64_ + (mixed ? 7 * b32_ : 0) + (size_t)nc_ * 16 + scal + 512 + 255) / 256 * 256;
 }
@@ -1374,7 +1426,8 @@ bool BsStored::setup(char *a, sgn_stats *stp)
     q = reinterpret_cast<char *>(((uintptr_t)q + 255) & ~(uintptr_t)255);
     spart_ = reinterpret_cast<z64 *>(q);
     vpart_ = spart_ + nst_;
-    S_ = reinterpret_cast<BsState *>(vpart_ + nvp);
+    rpart_ = vpart_ + nvp;
+    S_ = reinterpret_cast<BsState *>(rpart_ + 2 * (size_t)kMaxBlocks);
     hist_ = reinterpret_cast<BsHist *>(S_ + 1);
     rtab_ = reinterpret_cast<void **>(hist_ + maxiter_);
     stab_ = rtab_ + maxiter_ + poll_ + 2;
@@ -1688,6 +1741,7 @@ class BsBatch {
     size_t dcap_[3] = {0, 0, 0};
     StencilBatch stb_[3][4];
     int nvb_max_[3] = {0, 0, 0}, nxp_max_[3] = {0, 0, 0};
+    int fused_[3] = {0, 0, 0};           // alpha and omega are taken inside the phase's vector kernels
     double vbytes_[3] = {0, 0, 0};       // bytes of one element pass of every problem of the phase
     hipGraphExec_t gexec_ = nullptr;
     // host <-> device traffic of the polls: the problems' state pointers, their heads gathered in
@@ -1744,7 +1798,7 @@ void BsBatch::rebuild()
             j4.ep.norm = true;
             jobs[3].push_back(j4);
             desc[j] = BsDesc{b.S_, b.rtab_, b.stab_, p, v, sv, t, rh, (double2 *)b.x64_, b.spart_, b.vpart_,
-                             b.hist_, b.n_, (int)b.Sst_, 0, 0, b.maxiter_};
+                             b.rpart_, b.hist_, b.n_, (int)b.Sst_, 0, 0, b.maxiter_};
             nvb_max_[ph] = std::max(nvb_max_[ph], b.nvb_);
             nxp_max_[ph] = std::max(nxp_max_[ph], f ? vec_blocks(6 * b.Sst_) : b.nvb_);
             vbytes_[ph] += (double)b.n_ * (f ? 8.0 : 16.0);
@@ -1755,6 +1809,9 @@ void BsBatch::rebuild()
             desc[j].nb_s = stb_[ph][1].blocks(j);
             desc[j].nb_v = stb_[ph][3].blocks(j);
         }
+        fused_[ph] = 1;
+        for (const BsDesc &d : desc)
+            if (std::max(d.nb_s, d.nb_v) > kBsFusedPartials) fused_[ph] = 0;
         if (g.empty()) continue;
         const size_t need = sizeof(BsDesc) * g.size();
         if (need > dcap_[ph]) {
@@ -1778,21 +1835,22 @@ void BsBatch::launch_iteration(hipStream_t strm)
         const double nvec = vbytes_[ph] / (f ? 8.0 : 16.0);  // complex entries of all the phase's problems
         stb_[ph][0].launch(strm);
         stb_[ph][1].launch(strm);
-        hipLaunchKernelGGL(bs_alpha_batch, dim3(np), dim3(256), 0, strm, d);
+        const int fused = fused_[ph];
+        if (!fused) hipLaunchKernelGGL(bs_alpha_batch, dim3(np), dim3(256), 0, strm, d);
         int pr = ctx_->prof_start(strm, SGN_K_SEED_UPDATE, true);
         if (f)
-            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d);
+            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
         else
-            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d);
+            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
         ctx_->prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * vbytes_[ph], 8.0 * nvec);
         stb_[ph][2].launch(strm);
         stb_[ph][3].launch(strm);
-        hipLaunchKernelGGL(bs_omega_batch, dim3(np), dim3(256), 0, strm, d);
+        if (!fused) hipLaunchKernelGGL(bs_omega_batch, dim3(np), dim3(256), 0, strm, d);
         pr = ctx_->prof_start(strm, SGN_K_SEED_UPDATE, true);
         if (f)
-            launch_k(ctx_->prof_stamp(pr), bs_res_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d);
+            launch_k(ctx_->prof_stamp(pr), bs_res_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
         else
-            launch_k(ctx_->prof_stamp(pr), bs_res_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d);
+            launch_k(ctx_->prof_stamp(pr), bs_res_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
         ctx_->prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * vbytes_[ph], 12.0 * nvec);
         hipLaunchKernelGGL(bs_beta_batch, dim3(np), dim3(256), 0, strm, d, nvb_max_[ph]);
         pr = ctx_->prof_start(strm, SGN_K_SHIFT_UPDATE, true);

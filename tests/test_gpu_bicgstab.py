@@ -198,3 +198,20 @@ def test_full_size_bench_configuration_residuals_with_oracle_operator():
     e = _rel(x_bench, x)
     print(f"  unverified (benchmark) result vs verified: {e:.2e}", flush=True)
     assert e < 5e-9
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16, 16), (16, 16, 16, 17)])
+@pytest.mark.parametrize("nprob", [1, 2])
+def test_either_side_of_the_fused_scalar_steps(dims, nprob):
+    # FP32 dotting stencils leave one partial sum per 64 sites (and one for the padding): up to 1024 of them
+    # every block of the vector kernels adds them, above it is a launch of its own (65536 and 69632 sites)
+    lat = lattice(synth.gauge_field(dims, 0.4, 3), dims)
+    rf = sgn.sgn_rational_neuberger(16, 0.12, 2.6)
+    bs = [dev(synth.gaussian_source(dims, k).ravel()) for k in range(nprob)]
+
+    def solve(prec):
+        probs = [sgn.Problem(lat, 0.1 + 0.1 * k, b, torch.empty_like(b)) for k, b in enumerate(bs)]
+        sgn.multishift_bicgstab(probs, rf, tol=1e-10, prec=prec, theta32=1e-4)
+        return [host(p.x) for p in probs]
+    for x64, x32 in zip(solve(sgn.F64), solve(sgn.F32)):
+        assert np.linalg.norm(x32 - x64) / np.linalg.norm(x64) < 1e-8
