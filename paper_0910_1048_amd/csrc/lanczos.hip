@@ -46,25 +46,35 @@ struct LzScalars {
     int *flag;   // [k]   breakdown flags
 };
 
-__device__ __forceinline__ void lz_alpha_body(const z64 *partials, int nblk, const LzScalars &S, int j)
+// alpha_j = conj(t_j) s_j wh_j^H u from the dotting stencil's partials, in every thread of the block; store:
+// this block writes it to the table
+__device__ __forceinline__ z64 lz_alpha_body(const z64 *partials, int nblk, const LzScalars &S, int j, bool store)
 {
+    const z64 sv = S.sv[j], tw = S.tw[j];
     double re = 0.0, im = 0.0;
     for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
         re += partials[i].r;
         im += partials[i].i;
     }
     __shared__ double lds[8];
+    __shared__ z64 al;
     double v[2] = {re, im};
     block_sum<2>(v, lds);
     if (threadIdx.x == 0) {
         const z64 d = {v[0], v[1]};
-        S.alpha[j] = S.sv[j].r * cmulc(S.tw[j], d);  // conj(t_j) s_j (wh^H u)
+        al = sv.r * cmulc(tw, d);
+        if (store) S.alpha[j] = al;
     }
+    __syncthreads();
+    return al;
 }
 __global__ void lz_alpha_kernel(const z64 *partials, int nblk, LzScalars S, int j)
 {
-    lz_alpha_body(partials, nblk, S, j);
+    lz_alpha_body(partials, nblk, S, j, true);
 }
+// Up to this many partials every block of the update adds them itself (one launch less per step: 2.4 us and a
+// gap on 8^4); above, the re-reads cost more than the launch of lz_alpha_kernel.
+constexpr int kLzFusedPartials = 1024;
 
 __device__ __forceinline__ void lz_step_body(const z64 *partials, int nblk, const LzScalars &S, int j, double tol)
 {
@@ -111,11 +121,13 @@ __device__ __forceinline__ void lz_update_body(const void *u_, const void *z_, c
                                                const double2 *wj, const double2 *wjm, double2 *vn, double2 *wn,
                                                float4 *vn32, float4 *wn32, double2 *vc, double2 *wc,
                                                const LzScalars &S, int j, int V /* component stride */,
-                                               z64 *partials)
+                                               z64 *partials, const z64 *apart, int na)
 {
-    // coefficients of the two three-term recurrences
+    // coefficients of the two three-term recurrences (alpha_j from the na partials of apart, or with na = 0
+    // from the table)
     const double s0 = S.sv[j].r;
-    const z64 al = S.alpha[j], t0 = S.tw[j];
+    const z64 t0 = S.tw[j];
+    const z64 al = na > 0 ? lz_alpha_body(apart, na, S, j, blockIdx.x == 0) : S.alpha[j];
     const z64 cu = {s0, 0.0};
     const z64 cv0 = -(s0 * al);
     const z64 cz = t0;
@@ -184,9 +196,9 @@ __global__ void __launch_bounds__(256) lz_update_kernel(const void *u_, const vo
                                                         const double2 *vjm, const double2 *wj, const double2 *wjm,
                                                         double2 *vn, double2 *wn, float4 *vn32, float4 *wn32,
                                                         double2 *vc, double2 *wc, LzScalars S, int j, int V,
-                                                        z64 *partials)
+                                                        z64 *partials, const z64 *apart, int na)
 {
-    lz_update_body<F32>(u_, z_, vj, vjm, wj, wjm, vn, wn, vn32, wn32, vc, wc, S, j, V, partials);
+    lz_update_body<F32>(u_, z_, vj, vjm, wj, wjm, vn, wn, vn32, wn32, vc, wc, S, j, V, partials, apart, na);
 }
 
 constexpr int kLiftChunk = 64;
@@ -429,7 +441,8 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
 
         const int nst = dslash_blocks(lat);
         const int nvb = vec_blocks(6 * Sst);
-        z64 *part = static_cast<z64 *>(ctx.ensure_partials(sizeof(z64) * std::max(nst, 2 * nvb)));
+        z64 *part = static_cast<z64 *>(ctx.ensure_partials(sizeof(z64) * (nst + 2 * (size_t)nvb)));
+        z64 *vpart = part + nst;  // the update's (read by the step kernel while the update reads the stencil's)
         OpSpec opA, opAh;
         opA.mu = mu;
         opAh.mu = -mu;
@@ -472,7 +485,8 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
             ep.w = f32 ? w32.p : Wj(j);
             ep.partials = part;
             const int nb1 = dslash_launch(lat, sp, opA, f32 ? v32.p : Vj(j), f32 ? u32.p : u.p, ep, s);
-            hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s, part, nb1, S, j);
+            const int na = j + 1 < last && nb1 <= kLzFusedPartials ? nb1 : 0;
+            if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s, part, nb1, S, j);
             if (j + 1 == last) return;
             if (!two_pass) basis.ensure(j + 1);
             dslash_launch(lat, sp, opAh, f32 ? w32.p : Wj(j), f32 ? z32.p : z.p, Epilogue{}, s);
@@ -483,13 +497,13 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
                 hipLaunchKernelGGL(lz_update_kernel<true>, dim3(nvb), dim3(256), 0, s, u32.p, z32.p,
                                    (const double2 *)Vj(j), vjm, (const double2 *)Wj(j), wjm, (double2 *)vn,
                                    (double2 *)Wj(j + 1), (float4 *)v32.p, (float4 *)w32.p, (double2 *)nullptr,
-                                   (double2 *)nullptr, S, j, (int)Sst, part);
+                                   (double2 *)nullptr, S, j, (int)Sst, vpart, (const z64 *)part, na);
             else
                 hipLaunchKernelGGL(lz_update_kernel<false>, dim3(nvb), dim3(256), 0, s, u.p, z.p,
                                    (const double2 *)Vj(j), vjm, (const double2 *)Wj(j), wjm, (double2 *)vn,
                                    (double2 *)Wj(j + 1), (float4 *)nullptr, (float4 *)nullptr, (double2 *)nullptr,
-                                   (double2 *)nullptr, S, j, (int)Sst, part);
-            hipLaunchKernelGGL(lz_step_kernel, dim3(1), dim3(256), 0, s, part, nvb, S, j, 1e-14);
+                                   (double2 *)nullptr, S, j, (int)Sst, vpart, (const z64 *)part, na);
+            hipLaunchKernelGGL(lz_step_kernel, dim3(1), dim3(256), 0, s, vpart, nvb, S, j, 1e-14);
             SGN_HIP(hipGetLastError());
         };
 
@@ -679,7 +693,7 @@ class QmrSolve {
     std::unique_ptr<DevBuf> rcan_, y_, tmp_, Wb_, u_, z_, v32_, w32_, t32_, u32_, z32_, scal_;
     std::unique_ptr<PooledBasis> basis_;
     LzScalars S_{};
-    z64 *part_ = nullptr;
+    z64 *part_ = nullptr, *vpart_ = nullptr;  // of the dotting stencil and of the update
     std::vector<QmrShift> G_;
     std::vector<z64> halpha_, hsub_, hsup_;
     std::vector<int> hflag_;
@@ -799,7 +813,8 @@ bool QmrSolve::setup(sgn_stats *st, bool batch)
         dslots_ = dslot_buf_->as<void *>();
         ensure_slots(0);
     } else {
-        part_ = static_cast<z64 *>(ctx_.ensure_partials(sizeof(z64) * std::max(nst_, 2 * nvb_)));
+        part_ = static_cast<z64 *>(ctx_.ensure_partials(sizeof(z64) * (nst_ + 2 * (size_t)nvb_)));
+        vpart_ = part_ + nst_;
     }
     G_.assign(ns_, QmrShift{});
     for (int i = 0; i < ns_; ++i) {
@@ -827,7 +842,8 @@ void QmrSolve::step(int j)
     ep.w = f32 ? w32_->p : Wj(j);
     ep.partials = part_;
     const int nb1 = dslash_launch(lat_, sp_, opA_, f32 ? t32_->p : tmp, f32 ? u32_->p : u, ep, s_);
-    hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s_, part_, nb1, S_, j);
+    const int na = nb1 <= kLzFusedPartials ? nb1 : 0;
+    if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s_, part_, nb1, S_, j);
     dslash_launch(lat_, sp_, opAh_, f32 ? w32_->p : Wj(j), f32 ? t32_->p : tmp, Epilogue{}, s_);
     Epilogue ez;  // z = c^2 H^H (H^H wh_j)
     ez.a = c2_;
@@ -839,15 +855,15 @@ void QmrSolve::step(int j)
         launch_k(ctx_.prof_stamp(pr), lz_update_kernel<true>, dim3(nvb_), dim3(256), 0u, s_, u32_->p, z32_->p,
                            (const double2 *)basis[j], vjm, (const double2 *)Wj(j), wjm, (double2 *)basis[j + 1],
                            (double2 *)Wj(j + 1), (float4 *)v32_->p, (float4 *)w32_->p, (double2 *)nullptr,
-                           (double2 *)nullptr, S_, j, (int)Sst_, part_);
+                           (double2 *)nullptr, S_, j, (int)Sst_, vpart_, (const z64 *)part_, na);
     else
         launch_k(ctx_.prof_stamp(pr), lz_update_kernel<false>, dim3(nvb_), dim3(256), 0u, s_, u, z, (const double2 *)basis[j],
                            vjm, (const double2 *)Wj(j), wjm, (double2 *)basis[j + 1], (double2 *)Wj(j + 1),
                            (float4 *)nullptr, (float4 *)nullptr, (double2 *)nullptr, (double2 *)nullptr, S_, j,
-                           (int)Sst_, part_);
+                           (int)Sst_, vpart_, (const z64 *)part_, na);
     const double io = (f32 ? 2.0 * b32_ : 2.0 * i64_) + (j > 0 ? 4.0 : 2.0) * i64_ + 2.0 * i64_ + (f32 ? 2.0 * b32_ : 0.0);
     ctx_.prof_stop(pr, s_, SGN_K_SEED_UPDATE, io, 40.0 * ni_);
-    hipLaunchKernelGGL(lz_step_kernel, dim3(1), dim3(256), 0, s_, part_, nvb_, S_, j, 1e-14);
+    hipLaunchKernelGGL(lz_step_kernel, dim3(1), dim3(256), 0, s_, vpart_, nvb_, S_, j, 1e-14);
     SGN_HIP(hipGetLastError());
 }
 
@@ -1049,11 +1065,11 @@ __global__ void __launch_bounds__(256) qb_alpha_batch(const QbDesc *d)
 {
     const QbDesc &D = d[blockIdx.x];
     if (*D.done) return;
-    lz_alpha_body(D.part1, D.nb1, D.S, *D.step);
+    lz_alpha_body(D.part1, D.nb1, D.S, *D.step, true);
 }
 
 template <bool F32>
-__global__ void __launch_bounds__(256) qb_update_batch(const QbDesc *d)
+__global__ void __launch_bounds__(256) qb_update_batch(const QbDesc *d, int fused)
 {
     const QbDesc &D = d[blockIdx.y];
     if (*D.done) return;
@@ -1062,7 +1078,8 @@ __global__ void __launch_bounds__(256) qb_update_batch(const QbDesc *d)
     const double2 *vjm = j > 0 ? static_cast<const double2 *>(D.slots[j - 1]) : nullptr;
     lz_update_body<F32>(D.u, D.z, vj, vjm, D.W[j % 3], j > 0 ? D.W[(j + 2) % 3] : nullptr,
                         static_cast<double2 *>(D.slots[j + 1]), D.W[(j + 1) % 3], D.v32, D.w32,
-                        F32 ? nullptr : D.vcur, F32 ? nullptr : D.wcur, D.S, j, D.Sst, D.part2);
+                        F32 ? nullptr : D.vcur, F32 ? nullptr : D.wcur, D.S, j, D.Sst, D.part2, D.part1,
+                        fused ? D.nb1 : 0);
 }
 
 // nb: the grid width of the update that wrote the partials
@@ -1123,6 +1140,7 @@ class QmrBatch {
     size_t dcap_[3] = {0, 0, 0};
     StencilBatch stb_[3][4];
     int nvb_max_[3] = {0, 0, 0};
+    int fused_[3] = {0, 0, 0};  // alpha is taken inside the phase's update
     hipGraphExec_t gexec_ = nullptr;
     // the chunk's coefficients of every problem: scalar tables and a gather buffer (device), and
     // the pinned host mirror
@@ -1180,6 +1198,9 @@ void QmrBatch::rebuild()
             desc[j].nb1 = stb_[ph][1].blocks(j);
             desc[j].slots = q.dslots_;
         }
+        fused_[ph] = 1;
+        for (const QbDesc &d : desc)
+            if (d.nb1 > kLzFusedPartials) fused_[ph] = 0;
         const size_t need = sizeof(QbDesc) * g.size();
         if (need > dcap_[ph]) {
             if (ddesc_[ph]) SGN_HIP(hipFree(ddesc_[ph]));
@@ -1200,13 +1221,14 @@ void QmrBatch::launch_step(hipStream_t strm)
         const QbDesc *d = ddesc_[ph];
         stb_[ph][0].launch(strm);
         stb_[ph][1].launch(strm);
-        hipLaunchKernelGGL(qb_alpha_batch, dim3(np), dim3(256), 0, strm, d);
+        const int fused = fused_[ph];
+        if (!fused) hipLaunchKernelGGL(qb_alpha_batch, dim3(np), dim3(256), 0, strm, d);
         stb_[ph][2].launch(strm);
         stb_[ph][3].launch(strm);
         if (ph >= 1)
-            hipLaunchKernelGGL(qb_update_batch<true>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d);
+            hipLaunchKernelGGL(qb_update_batch<true>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d, fused);
         else
-            hipLaunchKernelGGL(qb_update_batch<false>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d);
+            hipLaunchKernelGGL(qb_update_batch<false>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d, fused);
         hipLaunchKernelGGL(qb_step_batch, dim3(np), dim3(256), 0, strm, d, nvb_max_[ph]);
     }
     SGN_HIP(hipGetLastError());
