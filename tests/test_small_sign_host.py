@@ -100,3 +100,35 @@ def test_baseline_isa_build_matches_oracle():
     err = float(out.stdout.strip().splitlines()[-1])
     print(f"baseline build: rel err {err:.1e}")
     assert err < 1e-11
+
+
+def _random_tridiagonal(rng, k, re_min=0.5):
+    d = np.where(rng.random(k) < 0.5, -1, 1) * rng.uniform(re_min, 2, k) + 0.2j * rng.standard_normal(k)
+    lo = 0.1 * (rng.standard_normal(k - 1) + 1j * rng.standard_normal(k - 1))
+    up = 0.1 * (rng.standard_normal(k - 1) + 1j * rng.standard_normal(k - 1))
+    return d, lo, up
+
+
+@pytest.mark.parametrize("k", [23, 24, 25, 64, 150])
+@pytest.mark.parametrize("kind", ["wide", "near axis", "decoupled"])
+def test_both_routes_at_their_boundary(k, kind, rng):
+    """24 is the smallest size of the rational route; an eigenvalue within 1e-3 of the imaginary axis and
+    modulus 1 needs more poles than it takes (the Schur form then), and zero couplings split T."""
+    d, lo, up = _random_tridiagonal(rng, k)
+    if kind == "near axis":
+        d[k // 2], lo[k // 2 - 1:k // 2 + 1], up[k // 2 - 1:k // 2 + 1] = 1e-3 + 1j, 1e-2, 1e-2
+    if kind == "decoupled":
+        lo[k // 3], up[2 * k // 3] = 0.0, 0.0
+    T = np.diag(d) + np.diag(lo, -1) + np.diag(up, 1)
+    y, mr = sgn.sgn_small_sign(d, lo, up)
+    # the oracle's error scales with the inverse distance of the eigenvalues on either side of the axis
+    assert rel(y, krylov.small_sign_e1(T)) < (1e-9 if kind == "near axis" else 1e-11)
+    assert mr == pytest.approx(np.min(np.abs(np.linalg.eigvals(T).real)), rel=1e-8)
+
+
+def test_axis_eigenvalue_in_a_large_matrix_is_refused(rng):
+    d, lo, up = _random_tridiagonal(rng, 40)
+    d[0], lo[0], up[0] = 0.7j, 0.0, 0.0
+    with pytest.raises(sgn.SgnError) as e:
+        sgn.sgn_small_sign(d, lo, up)
+    assert e.value.status == 6
