@@ -178,13 +178,19 @@ void host_sums(const z64 *dpart, int nb, hipStream_t s, zc &a, zc &b)
     }
 }
 
+// the sum of a dotting stencil's partials (packed), on the host
 zc host_sum1(const z64 *dpart, int nb, hipStream_t s)
 {
-    std::vector<z64> h(nb);
-    SGN_HIP(hipMemcpyAsync(h.data(), dpart, sizeof(z64) * nb, hipMemcpyDeviceToHost, s));
+    const int np = partial_count(nb), width = partial_width(nb);
+    std::vector<z64> h((size_t)np * width);
+    SGN_HIP(hipMemcpyAsync(h.data(), dpart, sizeof(z64) * h.size(), hipMemcpyDeviceToHost, s));
     SGN_HIP(hipStreamSynchronize(s));
     zc a = 0.0;
-    for (int k = 0; k < nb; ++k) a += zc(h[k].r, h[k].i);
+    for (int i = 0; i < np; ++i) {
+        zc t(h[(size_t)i * width].r, h[(size_t)i * width].i);
+        for (int q = 1; q < width; ++q) t += zc(h[(size_t)i * width + q].r, h[(size_t)i * width + q].i);
+        a += t;
+    }
     return a;
 }
 
@@ -534,9 +540,12 @@ __device__ __forceinline__ bool bs_alpha_body(BsState *S, const z64 *part, int n
     const int done = S->h.done, ns = S->h.ns, i = threadIdx.x;
     const z64 rho = S->h.rho, ap = S->h.alpha_prev, bp = S->h.beta_prev;
     double re = 0.0, im = 0.0;
-    for (int b = i; b < nb; b += blockDim.x) {
-        re += part[b].r;
-        im += part[b].i;
+    const int np = partial_count(nb), width = partial_width(nb);
+    for (int b = i; b < np; b += blockDim.x) {
+        z64 t[1];
+        partial_sum(part, b, width, t);
+        re += t[0].r;
+        im += t[0].i;
     }
     int act = 0;
     z64 z = {0.0, 0.0}, zp = {0.0, 0.0};
@@ -619,10 +628,13 @@ __device__ __forceinline__ bool bs_omega_body(BsState *S, const z64 *part, int n
 {
     const int done = S->h.done;  // not written by the kernels this runs in
     double a = 0.0, b = 0.0, c = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) {
-        a += part[2 * i].r;
-        b += part[2 * i].i;
-        c += part[2 * i + 1].r;
+    const int np = partial_count(nb), width = partial_width(nb);
+    for (int i = threadIdx.x; i < np; i += blockDim.x) {
+        z64 t[2];
+        partial_sum(part, i, width, t);
+        a += t[0].r;
+        b += t[0].i;
+        c += t[1].r;
     }
     if (done) return false;
     __shared__ double lds[12];
@@ -946,7 +958,7 @@ struct BsDesc {
     BsHist *hist;
     int64_t n;   // complex entries (12 S)
     int Sst;
-    int nb_s;    // blocks (partials) of the stencil that forms v, and of the one that forms t
+    int nb_s;    // partials (packed) of the stencil that forms v, and of the one that forms t
     int nb_v;
     int cap;     // history capacity (maxiter)
 };
@@ -1165,7 +1177,7 @@ void BsStored::launch_iteration(hipStream_t strm)
     e2.w = rh;
     e2.partials = spart_;
     const int nb = dslash_launch(lat_, sp, op, tmp, v, e2, strm);
-    const bool fused = nb <= kBsFusedPartials;  // both dotting stencils have the same blocks
+    const bool fused = partial_count(nb) * partial_width(nb) <= kBsFusedPartials;  // the same for both dotting stencils
     if (!fused) hipLaunchKernelGGL(bs_alpha_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)spart_, nb);
     const int nbs = fused ? nb : 0;
     const int pr = ctx_.prof_start(strm, SGN_K_SEED_UPDATE, true);
@@ -1811,7 +1823,8 @@ void BsBatch::rebuild()
         }
         fused_[ph] = 1;
         for (const BsDesc &d : desc)
-            if (std::max(d.nb_s, d.nb_v) > kBsFusedPartials) fused_[ph] = 0;
+            for (int nb : {d.nb_s, d.nb_v})
+                if (partial_count(nb) * partial_width(nb) > kBsFusedPartials) fused_[ph] = 0;
         if (g.empty()) continue;
         const size_t need = sizeof(BsDesc) * g.size();
         if (need > dcap_[ph]) {

@@ -89,6 +89,9 @@ struct StencilParams {
     int blk_sites;   // staged kernel: sites per block and t-slice (whole x-rows)
     int tslices;     // staged kernel: t-slices per block (1, or 2: a brick of the same B sites at t and t + 1)
     int nblk_total;  // blocks of this application (sites + padding); batched launches skip the rest
+    // split kernel with a dot product: the blocks are the wavefronts of the staged kernel's blocks (grp_n blocks of
+    // grp_sites sites, grp_waves wavefronts each; grp_waves = 0: 64 consecutive sites per block)
+    int grp_sites, grp_waves, grp_n;
     int link_ne;     // complex entries stored per link (6 or 9)
     int tgauge;      // temporal gauge: U_t = 1 off the last time slice (the staged and split kernels skip those links)
     int nrhs;        // right-hand sides of this application (staged kernel; the unstaged one uses NR)
@@ -941,33 +944,34 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
                 for (int k = 0; k < 12; ++k) zero[k] = {R(0), R(0)};
                 store_spinor(static_cast<SpT<R> *>(Q.out), P.S, s, zero);
             }
-            if constexpr (kDot) {
-                if (threadIdx.x == 0 && Q.w) {
-                    if (Q.norm) {
-                        Q.partials[2 * bx] = {0.0, 0.0};
-                        Q.partials[2 * bx + 1] = {0.0, 0.0};
-                    } else {
-                        Q.partials[bx] = {0.0, 0.0};
-                    }
-                }
-            }
         }
         return;
     }
     __shared__ __align__(16) cpx<R> chi_lds[8 * 6 * kSplitSites];
-    __shared__ __align__(16) cpx<R> out_lds[kCanon ? 13 * kSplitSites : 1];  // rows of 12, padded by one
+    __shared__ __align__(16) cpx<R> out_lds[kCanon || kDot ? 13 * kSplitSites : 1];  // rows of 12, padded by one
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // block bx0 of the launch; with a dot product one wavefront `part` of the staged kernel's block bx0 (on the
+    // same XCD)
+    int bx0 = bx, part = 0, sites = kSplitSites, nblk = P.nblk_sites, stride = kSplitSites;
+    if (kDot && P.grp_waves > 0) {
+        bx0 = bx / (8 * P.grp_waves) * 8 + bx % 8;
+        part = bx / 8 % P.grp_waves;
+        nblk = P.grp_n;
+        stride = P.grp_sites;
+        sites = min(kSplitSites, P.grp_sites - part * kSplitSites);
+        if (bx0 >= nblk) return;  // uniform
+    }
     int blk;
     if (P.sched_T > 0) {  // t fastest inside each XCD's t-slab (as the staged kernel)
-        const int k = bx % 8, j = bx / 8;
+        const int k = bx0 % 8, j = bx0 / 8;
         blk = (k * P.sched_T + j % P.sched_T) * P.sched_R + j / P.sched_T;
     } else {
-        blk = xcd_block(bx, P.nblk_sites);
+        blk = xcd_block(bx0, nblk);
     }
     // lanes past the last site work on it too (the register exchanges of the canonical form need every
     // lane) and store nothing
-    const int s0 = blk * kSplitSites, s = min(s0 + lane, P.V - 1);
-    const bool valid = s0 + lane < P.V;
+    const int s0 = blk * stride + part * kSplitSites, s = min(s0 + lane, P.V - 1);
+    const bool valid = lane < sites && s0 + lane < P.V;
     int c[4];
     {
         c[0] = s % P.L[0];
@@ -981,17 +985,15 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
         const RhsParams &Q = P.rhs[kMulti ? r : 0];
         if (r > 0) __syncthreads();  // the previous right-hand side's LDS reads are done
         const bool mine = wave < 6;  // this wavefront finishes component pair `wave`
-        cpx<R> acc[2] = {{R(0), R(0)}, {R(0), R(0)}}, zz[2], ww[2];
-        auto load_zw = [&]() {
-            if (kEpi && Q.z) load_pair(static_cast<const SpT<R> *>(Q.z), P.S, s, wave, zz);
-            if (kDot && Q.w && Q.w != Q.z) load_pair(static_cast<const SpT<R> *>(Q.w), P.S, s, wave, ww);
-        };
+        // wavefront 7 takes the dot product: the 12 components of its sites in order, as the staged kernel does
+        const bool dots = kDot && wave == 7;
+        cpx<R> acc[2] = {{R(0), R(0)}, {R(0), R(0)}}, zz[2], ww[kDot ? 12 : 1];
         // the operands of the second part: in flight during the hops, or, where the registers do not hold them
-        // as well (FP64), from the end of the hop on
+        // as well, from the end of the hop on
         if (mine) {
             if constexpr (kCanon) load_pair_canon(static_cast<const SpT<R> *>(Q.in), s, wave, acc);
             else load_pair(static_cast<const SpT<R> *>(Q.in), P.S, s, wave, acc);
-            if constexpr (sizeof(R) == 4) load_zw();
+            if (kEpi && sizeof(R) == 4 && Q.z) load_pair(static_cast<const SpT<R> *>(Q.z), P.S, s, wave, zz);
         }
         {
             cpx<R> chi[6];
@@ -1007,7 +1009,11 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
             }
 #pragma unroll
             for (int k = 0; k < 6; ++k) chi_lds[(wave * 6 + k) * kSplitSites + lane] = chi[k];
-            if (sizeof(R) == 8 && mine) load_zw();
+            if constexpr (kEpi || kDot) asm volatile("" ::: "memory");  // not during the hops: they would spill
+            if (kEpi && sizeof(R) == 8 && mine && Q.z) load_pair(static_cast<const SpT<R> *>(Q.z), P.S, s, wave, zz);
+            if constexpr (kDot) {
+                if (dots && Q.w) load_spinor(static_cast<const SpT<R> *>(Q.w), P.S, s, ww);
+            }
         }
         __syncthreads();
         double dr = 0.0, di = 0.0, dn = 0.0;
@@ -1055,23 +1061,11 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
                     }
                 }
             }
-            if constexpr (kCanon) {
+            if constexpr (kCanon || kDot) {
                 out_lds[lane * 13 + 2 * wave] = acc[0];
                 out_lds[lane * 13 + 2 * wave + 1] = acc[1];
-            } else if (valid) {
-                store_pair(static_cast<SpT<R> *>(Q.out), P.S, s, wave, acc);
             }
-            if constexpr (kDot) {
-                if (Q.w && valid) {
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const z64 a = cast<double>(Q.w == Q.z ? zz[k] : ww[k]), o = cast<double>(acc[k]);
-                        dr += a.r * o.r + a.i * o.i;
-                        di += a.r * o.i - a.i * o.r;
-                        dn += o.r * o.r + o.i * o.i;
-                    }
-                }
-            }
+            if (!kCanon && valid) store_pair(static_cast<SpT<R> *>(Q.out), P.S, s, wave, acc);
         }
         if constexpr (kCanon) {
             // the block's sites are one contiguous piece of the canonical output: written in order
@@ -1081,16 +1075,34 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
             for (int e = threadIdx.x; e < n; e += kSplitThreads) o[e] = out_lds[e / 12 * 13 + e % 12];
         }
         if constexpr (kDot) {
-            __shared__ double red[3 * (kSplitThreads / 64)];
-            if (Q.w) {  // uniform
-                double v[3] = {dr, di, dn};
-                block_sum<3>(v, red);
-                if (threadIdx.x == 0) {
+            __syncthreads();
+            if (dots && Q.w) {
+                double v[3] = {0.0, 0.0, 0.0};
+                if (valid) {
+                    // the products contracted as the compiler contracts finish_site's sums, which it does in
+                    // the other order for FP64
+                    constexpr bool kRealFirst = sizeof(R) == 8;
+                    double dr = 0.0, di = 0.0, dn = 0.0;
+#pragma unroll
+                    for (int k = 0; k < 12; ++k) {
+                        const z64 a = cast<double>(ww[k]), o = cast<double>(out_lds[lane * 13 + k]);
+                        dr += kRealFirst ? fma(a.i, o.i, a.r * o.r) : fma(a.r, o.r, a.i * o.i);
+                        di += fma(a.r, o.i, -(a.i * o.r));
+                        dn += kRealFirst ? fma(o.i, o.i, o.r * o.r) : fma(o.r, o.r, o.i * o.i);
+                    }
+                    v[0] = dr;
+                    v[1] = di;
+                    v[2] = dn;
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v[k] = wave_sum(v[k]);
+                if (lane == 0) {
+                    const int e = bx0 * P.grp_waves + part;
                     if (Q.norm) {
-                        Q.partials[2 * bx] = {v[0], v[1]};
-                        Q.partials[2 * bx + 1] = {v[2], 0.0};
+                        Q.partials[2 * e] = {v[0], v[1]};
+                        Q.partials[2 * e + 1] = {v[2], 0.0};
                     } else {
-                        Q.partials[bx] = {v[0], v[1]};
+                        Q.partials[e] = {v[0], v[1]};
                     }
                 }
             }
@@ -1098,15 +1110,21 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
     }
 }
 
-// (four waves per SIMD, i.e. two blocks per CU, for FP64 too: 128 VGPRs instead of 126-148)
+// Four waves per SIMD, i.e. two blocks per CU, for FP64 too (128 VGPRs); the batched FP64 epilogues would spill
+// there (up to 116 registers) and get two.
+template <typename R, bool kEpi, bool kMulti>
+constexpr int kSplitWaves = sizeof(R) == 8 && kEpi && kMulti ? 2 : 4;
+
 template <typename R, typename LT, bool kEpi, bool kDot, bool kCanon>
-__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4))) stencil_split_kernel(StencilParams P)
+__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(kSplitWaves<R, kEpi, false>)))
+    stencil_split_kernel(StencilParams P)
 {
     split_body<R, LT, kEpi, kDot, kCanon, false>(P, (int)blockIdx.x);
 }
 
 template <typename R, typename LT, bool kEpi, bool kDot>
-__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(4))) stencil_split_batch(const StencilParams *__restrict__ plist)
+__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(kSplitWaves<R, kEpi, true>)))
+    stencil_split_batch(const StencilParams *__restrict__ plist)
 {
     const StencilParams &P = plist[blockIdx.y];
     if ((int)blockIdx.x >= P.nblk_total) return;
@@ -1223,12 +1241,13 @@ StagedPlan staged_plan(const Lattice &lat, sgn_prec p, int max_threads = 0, int 
 
 }  // namespace
 
-// An upper bound of the blocks of any stencil launch on lat, whatever shape is chosen (tuned or
-// default): every staged block holds at least 64 sites, the unstaged kernel 256, and the padding
-// sites [V, S) take blocks of at least 64 threads.  Sizes the per-block partial sums.
+// An upper bound of the partial sums of any dotting stencil launch on lat, whatever shape is chosen (tuned or
+// default): one per block, every staged block holds at least 64 sites, the unstaged kernel 256, and the padding
+// sites [V, S) take blocks of at least 64 threads; the split kernel leaves one per wavefront of such a block,
+// at most two per 64 sites.
 int dslash_blocks(const Lattice &lat)
 {
-    const int64_t valid = (lat.V + 63) / 64;
+    const int64_t valid = 2 * ((lat.V + 63) / 64) + 4;
     const int64_t pad = lat.S > lat.V ? (lat.S - lat.V + 63) / 64 : 0;
     return (int)(valid + pad);
 }
@@ -1259,16 +1278,19 @@ struct PreparedStencil {
     StencilParams P{};
     StagedPlan pl;
     bool split = false;  // the split kernel (pl is then not used)
-    int nblk = 0;       // blocks of the launch (= partials written when dotting)
+    int nblk = 0;       // blocks of the launch
+    int partials = 0;   // partials written when dotting (packed)
     double bytes = 0.0;         // algorithmic bytes (links as nine entries) and flops
     double flops = 0.0;
     double bytes_stored = 0.0;  // bytes in the stored format (two-row links where the lattice keeps them)
     bool epi = false, dot = false;
 };
 
+enum KernelPick { kAuto, kStaged, kSplit };
+
 // max_threads > 0 caps the staged block (the register-link multi-RHS form)
 PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
-                                void *const *out, const Epilogue *ep, int max_threads = 0, bool canon = false)
+                                void *const *out, const Epilogue *ep, int max_threads = 0, KernelPick pick = kAuto)
 {
     if (nr < 1 || nr > kMaxRhs) throw Failure{SGN_ERR_INVALID, "stencil: 1..16 right-hand sides per launch"};
     PreparedStencil ps;
@@ -1334,8 +1356,25 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
     ps.flops = (1368.0 * nr + extra_flops) * lat.V;
     P.nrhs = nr;
     P.tslices = 1;
-    ps.split = canon || use_split(lat, p, nr > 1);
-    if (ps.split) {
+    ps.split = pick == kSplit || (pick == kAuto && use_split(lat, p, nr > 1));
+    P.grp_sites = P.grp_waves = P.grp_n = 0;
+    if (ps.split && ps.dot) {
+        // the blocks and wavefronts whose sums the staged kernel (or without a staged shape the unstaged one)
+        // would leave, in its block order: the dot products of a solve do not depend on the kernel
+        const StagedPlan pl = staged_plan(lat, p, max_threads);
+        const int64_t v3 = (int64_t)lat.L[0] * lat.L[1] * lat.L[2];
+        P.grp_sites = pl.ok ? pl.B : SGN_STENCIL_THREADS;
+        P.grp_waves = (P.grp_sites + kSplitSites - 1) / kSplitSites;
+        P.grp_n = (int)((lat.V + P.grp_sites - 1) / P.grp_sites);
+        P.sched_T = P.sched_R = 0;
+        if (v3 % P.grp_sites == 0 && lat.L[3] % 8 == 0) {
+            P.sched_T = lat.L[3] / 8;
+            P.sched_R = (int)(v3 / P.grp_sites);
+        }
+        P.nblk_sites = (P.grp_n + 7) / 8 * 8 * P.grp_waves;
+        ps.nblk = P.nblk_sites + (int)((lat.S - lat.V + kSplitThreads - 1) / kSplitThreads);
+        ps.partials = pack_partials(P.grp_n, P.grp_waves);
+    } else if (ps.split) {
         P.sched_T = P.sched_R = 0;
         const int64_t v3 = (int64_t)lat.L[0] * lat.L[1] * lat.L[2];
         if (v3 % kSplitSites == 0 && lat.L[3] % 8 == 0) {
@@ -1365,6 +1404,7 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
         }
     }
     P.nblk_total = ps.nblk;
+    if (!ps.partials) ps.partials = pack_partials(ps.nblk, 1);
     if (lat.gauge && (ps.pl.ok || ps.split)) {  // these kernels read the time links of the last slice only
         P.tgauge = 1;
         ps.bytes_stored -= (1.0 - 1.0 / lat.L[3]) * lat.link_ne * ((p == SGN_PREC_F64) ? 16.0 : (p == SGN_PREC_F32 ? 8.0 : 4.0)) * lat.V;
@@ -1434,7 +1474,7 @@ namespace {
 int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in, void *const *out,
                  const Epilogue *ep, hipStream_t s, bool canon)
 {
-    const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep, 0, canon);
+    const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep, 0, canon ? kSplit : kAuto);
     if (nr > 1 && (ps.pl.ok || ps.split)) {
         // several right-hand sides: the batched form, one group, parameters in device memory
         // (the lattice's batch object: they are uploaded when they change, after the device has
@@ -1444,7 +1484,7 @@ int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const
         if (!lat.multi) lat.multi = std::make_shared<StencilBatch>();
         lat.multi->prepare(jobs, p);
         lat.multi->launch(s);
-        return ps.nblk;
+        return ps.partials;
     }
     // one launch unless the unstaged kernel runs several right-hand sides
     const int prof = lat.ctx->prof_start(s, kclass(p), ps.pl.ok || nr == 1);
@@ -1477,7 +1517,7 @@ int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const
     }
     SGN_HIP(hipGetLastError());
     lat.ctx->prof_stop(prof, s, kclass(p), ps.bytes, ps.flops, false, ps.bytes_stored);
-    return ps.nblk;
+    return ps.partials;
 }
 
 }  // namespace
@@ -1507,7 +1547,7 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
 {
     jobs_ = jobs;
     prec_ = p;
-    nblk_.assign(jobs.size(), 0);
+    partials_.assign(jobs.size(), 0);
     batched_ = !jobs.empty();
     epi_ = dot_ = false;
     gx_ = threads_ = 0;
@@ -1518,10 +1558,17 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
     // sides one after another, so the group size is the largest (up to kMaxRhs) that still leaves
     // the launch 1024 blocks of sites (four per CU), or as many as groups of one would: small
     // lattices trade link sharing for parallelism
+    // The split kernel serves a launch whose fields together are small; with more of them the chip is full and
+    // the staged kernel's reuse wins (24 right-hand sides on 8^4, 12^4 and 16^4, FP32 with a dot product: 66 us
+    // staged, 77 split).  Dot products have the same bits either way.
+    double fields = 0.0;
+    for (const StencilJob &j : jobs) fields += (double)j.lat->V * (p == SGN_PREC_F64 ? 192 : 96);
+    const bool small = fields <= (double)kSplitMaxBytes;
     int gsize = kMaxRhs;
+    bool multi = false;  // whether the staged kernel would see a group of several right-hand sides
     {
         std::vector<const Lattice *> lats;
-        std::vector<int64_t> cnt, per;
+        std::vector<int64_t> cnt, per, per_staged;
         for (const StencilJob &j : jobs) {
             size_t l = 0;
             while (l < lats.size() && lats[l] != j.lat) ++l;
@@ -1530,19 +1577,26 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
                 cnt.push_back(0);
                 const Context::TunedShape ts = j.lat->ctx->tuned_shape(j.lat->L, p, true);
                 const StagedPlan pl = staged_plan(*j.lat, p, 0, ts.max_sites, ts.tslices);
-                per.push_back(use_split(*j.lat, p, true) ? (j.lat->V + kSplitSites - 1) / kSplitSites
-                              : pl.ok                    ? pl.nblk_sites
-                                                         : (j.lat->V + 255) / 256);
+                per_staged.push_back(pl.ok ? pl.nblk_sites : (j.lat->V + 255) / 256);
+                per.push_back(small && use_split(*j.lat, p, true) ? (j.lat->V + kSplitSites - 1) / kSplitSites
+                                                                  : per_staged.back());
             }
             ++cnt[l];
         }
-        auto blocks = [&](int g) {
-            int64_t b = 0;
-            for (size_t l = 0; l < lats.size(); ++l) b += (cnt[l] + g - 1) / g * per[l];
-            return b;
+        auto group_size = [&](const std::vector<int64_t> &blk) {
+            auto blocks = [&](int g) {
+                int64_t b = 0;
+                for (size_t l = 0; l < lats.size(); ++l) b += (cnt[l] + g - 1) / g * blk[l];
+                return b;
+            };
+            int g = kMaxRhs;
+            const int64_t want = std::min<int64_t>(1024, blocks(1));
+            while (g > 1 && blocks(g) < want) --g;
+            return g;
         };
-        const int64_t want = std::min<int64_t>(1024, blocks(1));
-        while (gsize > 1 && blocks(gsize) < want) --gsize;
+        gsize = group_size(per);
+        const int staged = group_size(per_staged);
+        for (int64_t c : cnt) multi = multi || std::min<int64_t>(c, staged) > 1;
     }
     std::vector<std::vector<size_t>> groups;
     for (size_t k = 0; k < jobs.size(); ++k) {
@@ -1552,27 +1606,27 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
         if (g == groups.size()) groups.emplace_back();
         groups[g].push_back(k);
     }
-    // the groups of small lattices first: they are the split kernel's launch, the others the staged kernel's
-    nsplit_ = (int)(std::stable_partition(groups.begin(), groups.end(),
-                                          [&](const std::vector<size_t> &g) {
-                                              return use_split(*jobs[g[0]].lat, p, g.size() > 1);
-                                          }) -
-                    groups.begin());
+    // the split kernel's groups first: two launches where a lattice has a staged shape tuned or pinned
+    auto split_group = [&](const std::vector<size_t> &g) {
+        return small && use_split(*jobs[g[0]].lat, p, g.size() > 1);
+    };
+    nsplit_ = (int)(std::stable_partition(groups.begin(), groups.end(), split_group) - groups.begin());
     gx_split_ = 0;
     // links in registers (FP16 two-row links, some group with several right-hand sides, and the
     // environment does not ask for re-reads: SGN_MULTI_LINK_REGS=0)
     regs_ = p == SGN_PREC_F32_H16;
-    bool multi = false;
-    for (size_t g = nsplit_; g < groups.size(); ++g) {
-        multi = multi || groups[g].size() > 1;
-        regs_ = regs_ && jobs[groups[g][0]].lat->link_ne == 6;
-    }
+    for (size_t g = 0; g < groups.size(); ++g) regs_ = regs_ && jobs[groups[g][0]].lat->link_ne == 6;
     {
         const char *e = std::getenv("SGN_MULTI_LINK_REGS");
-        const Lattice *l0 = (size_t)nsplit_ < groups.size() ? jobs[groups[nsplit_][0]].lat : nullptr;
-        const int tuned = l0 ? l0->ctx->tuned_shape(l0->L, p, true).regs : -1;
+        const int tuned = jobs.empty() ? -1 : jobs[0].lat->ctx->tuned_shape(jobs[0].lat->L, p, true).regs;
         regs_ = regs_ && multi && !(e && e[0] == '0') && tuned != 0;
     }
+    const int cap = regs_ ? kRegsMaxThreads : 0;
+    // the blocks whose sums a split dot product leaves (without a staged shape for some lattice every
+    // application would be a launch of its own, without the cap)
+    int dot_cap = cap;
+    for (size_t g = 0; g < groups.size(); ++g)
+        if (!staged_plan(*jobs[groups[g][0]].lat, p, cap).ok) dot_cap = 0;
     std::vector<StencilParams> host(groups.size());
     for (size_t g = 0; g < groups.size(); ++g) {
         const int nr = (int)groups[g].size();
@@ -1589,9 +1643,9 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
         }
         const Lattice &lat = *jobs[groups[g][0]].lat;
         const PreparedStencil ps = prepare_stencil(lat, p, nr, op.data(), in.data(), out.data(), ep.data(),
-                                                   regs_ ? kRegsMaxThreads : 0);
+                                                   (int)g < nsplit_ ? dot_cap : cap, (int)g < nsplit_ ? kSplit : kStaged);
         host[g] = ps.P;
-        for (size_t k : groups[g]) nblk_[k] = ps.nblk;
+        for (size_t k : groups[g]) partials_[k] = ps.partials;
         batched_ = batched_ && (ps.pl.ok || ps.split);
         epi_ = epi_ || ps.epi;
         dot_ = dot_ || ps.dot;
@@ -1609,7 +1663,13 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
     ngroups_ = (int)groups.size() - nsplit_;
     gx_ = (gx_ + 7) / 8 * 8;
     gx_split_ = (gx_split_ + 7) / 8 * 8;
-    if (!batched_) return;
+    if (!batched_) {  // launches of their own (see launch), and so the partials of those
+        for (size_t k = 0; k < jobs.size(); ++k) {
+            const StencilJob &j = jobs[k];
+            partials_[k] = prepare_stencil(*j.lat, p, 1, &j.op, &j.in, &j.out, &j.ep).partials;
+        }
+        return;
+    }
     const size_t need = sizeof(StencilParams) * host.size();
     // unchanged parameters stay on the device; new ones wait until no launch reads the old
     if (need == uploaded_.size() && std::memcmp(uploaded_.data(), host.data(), need) == 0) return;

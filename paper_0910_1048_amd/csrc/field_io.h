@@ -178,6 +178,27 @@ __device__ __forceinline__ void load_link(const LT *__restrict__ U, int S, int n
     }
 }
 
+// Partial sum j of a dotting stencil (see pack_partials): `width` consecutive entries of STRIDE values.
+// All loads are issued before the first use.
+template <int STRIDE>
+__device__ __forceinline__ void partial_sum(const z64 *__restrict__ part, int j, int width, z64 (&s)[STRIDE])
+{
+    const z64 *p = part + (size_t)j * width * STRIDE;
+#pragma unroll
+    for (int k = 0; k < STRIDE; ++k) s[k] = p[k];
+    if (width == 1) return;  // uniform
+    z64 v[kMaxPartialWidth - 1][STRIDE];
+#pragma unroll
+    for (int q = 1; q < kMaxPartialWidth; ++q)
+#pragma unroll
+        for (int k = 0; k < STRIDE; ++k) v[q - 1][k] = p[(q < width ? q : 0) * STRIDE + k];
+#pragma unroll
+    for (int q = 1; q < kMaxPartialWidth; ++q)
+#pragma unroll
+        for (int k = 0; k < STRIDE; ++k)
+            if (q < width) s[k] = s[k] + v[q - 1][k];
+}
+
 // XCD-aware block order: consecutive hardware block ids are dealt round-robin
 // to the 8 XCDs, so hardware block i is mapped to a logical block such that
 // each XCD walks one contiguous slab of the lattice (t-neighbours then mostly

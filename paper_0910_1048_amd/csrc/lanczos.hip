@@ -52,9 +52,12 @@ __device__ __forceinline__ z64 lz_alpha_body(const z64 *partials, int nblk, cons
 {
     const z64 sv = S.sv[j], tw = S.tw[j];
     double re = 0.0, im = 0.0;
-    for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
-        re += partials[i].r;
-        im += partials[i].i;
+    const int np = partial_count(nblk), width = partial_width(nblk);
+    for (int i = threadIdx.x; i < np; i += blockDim.x) {
+        z64 t[1];
+        partial_sum(partials, i, width, t);
+        re += t[0].r;
+        im += t[0].i;
     }
     __shared__ double lds[8];
     __shared__ z64 al;
@@ -485,7 +488,7 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
             ep.w = f32 ? w32.p : Wj(j);
             ep.partials = part;
             const int nb1 = dslash_launch(lat, sp, opA, f32 ? v32.p : Vj(j), f32 ? u32.p : u.p, ep, s);
-            const int na = j + 1 < last && nb1 <= kLzFusedPartials ? nb1 : 0;
+            const int na = j + 1 < last && partial_count(nb1) * partial_width(nb1) <= kLzFusedPartials ? nb1 : 0;
             if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s, part, nb1, S, j);
             if (j + 1 == last) return;
             if (!two_pass) basis.ensure(j + 1);
@@ -842,7 +845,7 @@ void QmrSolve::step(int j)
     ep.w = f32 ? w32_->p : Wj(j);
     ep.partials = part_;
     const int nb1 = dslash_launch(lat_, sp_, opA_, f32 ? t32_->p : tmp, f32 ? u32_->p : u, ep, s_);
-    const int na = nb1 <= kLzFusedPartials ? nb1 : 0;
+    const int na = partial_count(nb1) * partial_width(nb1) <= kLzFusedPartials ? nb1 : 0;
     if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s_, part_, nb1, S_, j);
     dslash_launch(lat_, sp_, opAh_, f32 ? w32_->p : Wj(j), f32 ? t32_->p : tmp, Epilogue{}, s_);
     Epilogue ez;  // z = c^2 H^H (H^H wh_j)
@@ -1200,7 +1203,7 @@ void QmrBatch::rebuild()
         }
         fused_[ph] = 1;
         for (const QbDesc &d : desc)
-            if (d.nb1 > kLzFusedPartials) fused_[ph] = 0;
+            if (partial_count(d.nb1) * partial_width(d.nb1) > kLzFusedPartials) fused_[ph] = 0;
         const size_t need = sizeof(QbDesc) * g.size();
         if (need > dcap_[ph]) {
             if (ddesc_[ph]) SGN_HIP(hipFree(ddesc_[ph]));

@@ -95,7 +95,7 @@ struct MsVec {
                          // residual that replaces slot temp_iter as input (after a reliable update)
     void *const *slots;  // stored-basis form: slot table, slot 0 = y; nullptr in per-shift form
     int temp_iter;       // stored-basis form: iteration whose seed update starts from r
-    int nst_part;        // partials written by the dotting stencil
+    int nst_part;        // partials (packed) written by the dotting stencil
     void *rt, *q, *qt, *pt;
     void *P, *X;         // the seed's p and x (stored basis) or those of every shift
     z64 *spart;          // partials of the dotting stencil
@@ -121,9 +121,12 @@ __global__ void __launch_bounds__(256) ms_alpha_kernel(const MsVec *vl, const in
     MsState *S = d.S;
     if (S->h.done) return;
     double re = 0.0, im = 0.0;
-    for (int i = threadIdx.x; i < d.nst_part; i += blockDim.x) {
-        re += d.spart[i].r;
-        im += d.spart[i].i;
+    const int np = partial_count(d.nst_part), width = partial_width(d.nst_part);
+    for (int i = threadIdx.x; i < np; i += blockDim.x) {
+        z64 t[1];
+        partial_sum(d.spart, i, width, t);
+        re += t[0].r;
+        im += t[0].i;
     }
     __shared__ double lds[8];
     __shared__ z64 alpha_sh;

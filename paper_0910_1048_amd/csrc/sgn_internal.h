@@ -220,8 +220,16 @@ struct Epilogue {
     bool norm = false;            // with w: also ||out||^2, partials[2b] = dot, partials[2b+1] = {norm, 0}
 };
 
-// Launch the stencil on internal-layout fields.  Returns the number of blocks
-// (= number of partials written when ep.w is set).
+// The partial sums that a dotting stencil leaves: n sums of `width` consecutive entries each (two values per
+// entry with Epilogue::norm), to be added in that order, packed into one int.  width > 1 where the launch wrote
+// one entry per wavefront of what is one block in the staged kernel: the sums then have the same bits
+// whichever kernel ran.
+constexpr int kMaxPartialWidth = 11;
+inline int pack_partials(int n, int width) { return n | (width - 1) << 24; }
+__host__ __device__ inline int partial_count(int p) { return p & 0xFFFFFF; }
+__host__ __device__ inline int partial_width(int p) { return (p >> 24) + 1; }
+
+// Launch the stencil on internal-layout fields.  Returns the partials written (packed) when ep.w is set.
 // nr (1..16) right-hand sides in one launch sharing every link load; each has
 // its own operator (mu, gamma5 flags), input, output and epilogue.
 int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
@@ -256,12 +264,12 @@ class StencilBatch {
     StencilBatch &operator=(const StencilBatch &) = delete;
     void prepare(const std::vector<StencilJob> &jobs, sgn_prec p);  // synchronous upload
     void launch(hipStream_t s) const;
-    int blocks(size_t k) const { return nblk_[k]; }  // partials written by application k
+    int blocks(size_t k) const { return partials_[k]; }  // partials (packed) written by application k
     size_t size() const { return jobs_.size(); }
 
   private:
     std::vector<StencilJob> jobs_;
-    std::vector<int> nblk_;
+    std::vector<int> partials_;
     sgn_prec prec_ = SGN_PREC_F64;
     void *dev_ = nullptr;
     size_t dev_bytes_ = 0;

@@ -58,3 +58,31 @@ def test_split_and_canonical_forms_are_the_same_operator(dims, prec, flags):
         return                                     # no staged block fits so small a lattice
     for a, c in zip(first, results()):
         assert torch.equal(a, c)
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32, sgn.F32_H16])
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (12, 12, 12, 6), (15, 13, 6, 4), (7, 9, 5, 8), (4, 4, 4, 4)])
+@pytest.mark.parametrize("nprob", [1, 2])
+def test_solves_have_the_same_bits_with_either_kernel(dims, prec, nprob):
+    """The dot products too: one entry per wavefront of the staged kernel's blocks (256, 288, 195, 315 and 256
+    FP64 sites: whole wavefronts and remainders), added in its order."""
+    lat = sgn.Lattice(ctx(), dev(synth.gauge_field(dims, 0.4, 1)), dims, 0.2)
+    rf = sgn.sgn_rational_neuberger(16, 0.12, 2.6)
+    bs = [dev(synth.gaussian_source(dims, k).ravel()) for k in range(nprob)]
+
+    def solve():
+        probs = [sgn.Problem(lat, 0.1 + 0.1 * k, b, torch.empty_like(b)) for k, b in enumerate(bs)]
+        st = sgn.multishift_bicgstab(probs, rf, tol=1e-10, prec=prec)
+        q = [sgn.Problem(lat, 0.1, b, torch.empty_like(b)) for b in bs]
+        sgn.multishift_qmr(q, rf, tol=1e-9)
+        m = [sgn.Problem(lat, 0.1, b, torch.empty_like(b)) for b in bs]
+        sgn.multishift_solve(m, rf, tol=1e-9)
+        return [p.x for p in probs + q + m], [s["iterations"] for s in st]
+    x, its = solve()
+    for p in (sgn.F64, sgn.F32, sgn.F32_H16):
+        sgn.sgn_tune_set(lat, p, False, 0, 1)
+        sgn.sgn_tune_set(lat, p, True, 0, 1)
+    y, its2 = solve()
+    assert its == its2
+    for a, c in zip(x, y):
+        assert torch.equal(a, c)
