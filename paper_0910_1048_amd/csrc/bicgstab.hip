@@ -528,6 +528,8 @@ __device__ __forceinline__ void stz_nt(float2 *p, int64_t e, z64 v)
 // fewer per iteration (8^4 FP64: s and r' updates with their scalars 13.0 -> 9.5 us, and two gaps less).  Above
 // kBsFusedPartials the re-reads cost more than a launch and one block does it alone.  beta keeps its own
 // launch (5.7 us): its code is long, and fetched by every CU it made the 3.4 us x, p update take 17 us.
+// The forms are kernels of their own: with a run-time choice the single-precision s update of 24^3 x 48 took 51 us
+// instead of 41 (6.3 TB/s).
 // All of them are bound by latency: the loads (the flags, the partials and, in the thread of each shift, that
 // shift's state) are issued before the first use.
 constexpr int kBsFusedPartials = 1024;
@@ -539,14 +541,8 @@ __device__ __forceinline__ bool bs_alpha_body(BsState *S, const z64 *part, int n
 {
     const int done = S->h.done, ns = S->h.ns, i = threadIdx.x;
     const z64 rho = S->h.rho, ap = S->h.alpha_prev, bp = S->h.beta_prev;
-    double re = 0.0, im = 0.0;
-    const int np = partial_count(nb), width = partial_width(nb);
-    for (int b = i; b < np; b += blockDim.x) {
-        z64 t[1];
-        partial_sum(part, b, width, t);
-        re += t[0].r;
-        im += t[0].i;
-    }
+    double v[2] = {0.0, 0.0};
+    add_partials<1>(part, nb, v);
     int act = 0;
     z64 z = {0.0, 0.0}, zp = {0.0, 0.0};
     double tau = 0.0;
@@ -559,7 +555,6 @@ __device__ __forceinline__ bool bs_alpha_body(BsState *S, const z64 *part, int n
     __shared__ double lds[8];
     __shared__ int bad;
     __shared__ z64 al_sh;
-    double v[2] = {re, im};
     block_sum<2>(v, lds);
     if (i == 0) {
         const z64 den = {v[0], v[1]};
@@ -592,14 +587,14 @@ __global__ void __launch_bounds__(256) bs_alpha_kernel(BsState *S, const z64 *pa
 }
 
 // s = r_k - alpha v (r_k read from its slot), into the work vector and the slot of iteration k
-// (nb > 0: alpha is taken from the nb partials here)
-template <typename R>
+// (kFused: alpha is taken from the nb partials here)
+template <typename R, bool kFused>
 __device__ __forceinline__ void bs_sub_stored_body(BsState *S, const z64 *part, int nb, void *const *rslots,
                               const typename BsVec<R>::t *v, typename BsVec<R>::t *s, void *const *sslots, int64_t n)
 {
     using T = typename BsVec<R>::t;
     z64 al;
-    if (nb > 0) {
+    if constexpr (kFused) {
         if (!bs_alpha_body(S, part, nb, blockIdx.x == 0, al)) return;
     } else {
         if (S->h.done) return;
@@ -615,11 +610,11 @@ __device__ __forceinline__ void bs_sub_stored_body(BsState *S, const z64 *part, 
         stz_nt(slot, e, sv);
     }
 }
-template <typename R>
+template <typename R, bool kFused>
 __global__ void __launch_bounds__(256) bs_sub_stored(BsState *S, const z64 *part, int nb, void *const *rslots,
                               const typename BsVec<R>::t *v, typename BsVec<R>::t *s, void *const *sslots, int64_t n)
 {
-    bs_sub_stored_body<R>(S, part, nb, rslots, v, s, sslots, n);
+    bs_sub_stored_body<R, kFused>(S, part, nb, rslots, v, s, sslots, n);
 }
 
 // omega = t^H s / t^H t (0 when t = 0: s was the exact residual 0), from the partials
@@ -627,19 +622,11 @@ __global__ void __launch_bounds__(256) bs_sub_stored(BsState *S, const z64 *part
 __device__ __forceinline__ bool bs_omega_body(BsState *S, const z64 *part, int nb, bool writer, z64 &om)
 {
     const int done = S->h.done;  // not written by the kernels this runs in
-    double a = 0.0, b = 0.0, c = 0.0;
-    const int np = partial_count(nb), width = partial_width(nb);
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        z64 t[2];
-        partial_sum(part, i, width, t);
-        a += t[0].r;
-        b += t[0].i;
-        c += t[1].r;
-    }
+    double v[3] = {0.0, 0.0, 0.0};  // s^H t and ||t||^2
+    add_partials<2>(part, nb, v);
     if (done) return false;
     __shared__ double lds[12];
     __shared__ z64 om_sh;
-    double v[3] = {a, b, c};
     block_sum<3>(v, lds);
     if (threadIdx.x == 0) {
         om_sh = v[2] > 0.0 ? z64{v[0] / v[2], -v[1] / v[2]} : z64{0.0, 0.0};
@@ -657,15 +644,15 @@ __global__ void __launch_bounds__(256) bs_omega_kernel(BsState *S, const z64 *pa
 
 // r' = s - omega t into the slot of iteration k + 1 (the residual lives only there);
 // partials of r^^H r' and ||r'||^2 (of the stored values)
-// (nb > 0: omega is taken from the nb partials of opart here)
-template <typename R>
+// (kFused: omega is taken from the nb partials of opart here)
+template <typename R, bool kFused>
 __device__ __forceinline__ void bs_res_stored_body(BsState *S, const z64 *opart, int nb, const typename BsVec<R>::t *s,
                               const typename BsVec<R>::t *t, const typename BsVec<R>::t *rh, void *const *rslots,
                               int64_t n, z64 *part)
 {
     using T = typename BsVec<R>::t;
     z64 om;
-    if (nb > 0) {
+    if constexpr (kFused) {
         if (!bs_omega_body(S, opart, nb, blockIdx.x == 0, om)) return;
     } else {
         if (S->h.done) return;
@@ -690,12 +677,12 @@ __device__ __forceinline__ void bs_res_stored_body(BsState *S, const z64 *opart,
         part[2 * blockIdx.x + 1] = {v[2], 0.0};
     }
 }
-template <typename R>
+template <typename R, bool kFused>
 __global__ void __launch_bounds__(256) bs_res_stored(BsState *S, const z64 *opart, int nb, const typename BsVec<R>::t *s,
                               const typename BsVec<R>::t *t, const typename BsVec<R>::t *rh, void *const *rslots,
                               int64_t n, z64 *part)
 {
-    bs_res_stored_body<R>(S, opart, nb, s, t, rh, rslots, n, part);
+    bs_res_stored_body<R, kFused>(S, opart, nb, s, t, rh, rslots, n, part);
 }
 
 // beta, the history entry, the shifted residual estimates and the control flags
@@ -981,21 +968,20 @@ __global__ void __launch_bounds__(256) bs_beta_batch(const BsDesc *d, int nb)
     const BsDesc &D = d[blockIdx.x];
     bs_beta_kernel_body(D.S, D.rpart, nb, D.hist, D.cap);
 }
-// fused: the scalar step inside the vector kernel
-template <typename R>
-__global__ void __launch_bounds__(256) bs_sub_batch(const BsDesc *d, int fused)
+template <typename R, bool kFused>
+__global__ void __launch_bounds__(256) bs_sub_batch(const BsDesc *d)
 {
     using T = typename BsVec<R>::t;
     const BsDesc &D = d[blockIdx.y];
-    bs_sub_stored_body<R>(D.S, D.spart, fused ? D.nb_s : 0, D.rtab, (const T *)D.v, (T *)D.sv, D.stab, D.n);
+    bs_sub_stored_body<R, kFused>(D.S, D.spart, D.nb_s, D.rtab, (const T *)D.v, (T *)D.sv, D.stab, D.n);
 }
-template <typename R>
-__global__ void __launch_bounds__(256) bs_res_batch(const BsDesc *d, int fused)
+template <typename R, bool kFused>
+__global__ void __launch_bounds__(256) bs_res_batch(const BsDesc *d)
 {
     using T = typename BsVec<R>::t;
     const BsDesc &D = d[blockIdx.y];
-    bs_res_stored_body<R>(D.S, D.vpart, fused ? D.nb_v : 0, (const T *)D.sv, (const T *)D.t, (const T *)D.rh, D.rtab,
-                          D.n, D.rpart);
+    bs_res_stored_body<R, kFused>(D.S, D.vpart, D.nb_v, (const T *)D.sv, (const T *)D.t, (const T *)D.rh, D.rtab, D.n,
+                                  D.rpart);
 }
 __global__ void __launch_bounds__(256) bs_xp64_batch(const BsDesc *d)
 {
@@ -1179,14 +1165,13 @@ void BsStored::launch_iteration(hipStream_t strm)
     const int nb = dslash_launch(lat_, sp, op, tmp, v, e2, strm);
     const bool fused = partial_count(nb) * partial_width(nb) <= kBsFusedPartials;  // the same for both dotting stencils
     if (!fused) hipLaunchKernelGGL(bs_alpha_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)spart_, nb);
-    const int nbs = fused ? nb : 0;
     const int pr = ctx_.prof_start(strm, SGN_K_SEED_UPDATE, true);
     if (f)
-        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<float>, dim3(nvb_), dim3(256), 0u, strm, S_,
-                           (const z64 *)spart_, nbs, (void *const *)rtab_, (const float2 *)v, (float2 *)sv, (void *const *)stab_, n_);
+        launch_k(ctx_.prof_stamp(pr), fused ? bs_sub_stored<float, true> : bs_sub_stored<float, false>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)spart_, nb, (void *const *)rtab_, (const float2 *)v, (float2 *)sv, (void *const *)stab_, n_);
     else
-        launch_k(ctx_.prof_stamp(pr), bs_sub_stored<double>, dim3(nvb_), dim3(256), 0u, strm, S_,
-                           (const z64 *)spart_, nbs, (void *const *)rtab_, (const double2 *)v, (double2 *)sv, (void *const *)stab_, n_);
+        launch_k(ctx_.prof_stamp(pr), fused ? bs_sub_stored<double, true> : bs_sub_stored<double, false>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)spart_, nb, (void *const *)rtab_, (const double2 *)v, (double2 *)sv, (void *const *)stab_, n_);
     ctx_.prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * (f ? 8.0 : 16.0) * n_, 8.0 * n_);
     dslash_launch(lat_, sp, op, sv, tmp, Epilogue{}, strm);
     Epilogue e4;  // t = M s with the partials of s^H t and ||t||^2
@@ -1202,12 +1187,12 @@ void BsStored::launch_iteration(hipStream_t strm)
     if (!fused) hipLaunchKernelGGL(bs_omega_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)vpart_, nb4);
     pr2 = ctx_.prof_start(strm, SGN_K_SEED_UPDATE, true);
     if (f)
-        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<float>, dim3(nvb_), dim3(256), 0u, strm, S_,
-                           (const z64 *)vpart_, fused ? nb4 : 0, (const float2 *)sv, (const float2 *)t, (const float2 *)rh,
+        launch_k(ctx_.prof_stamp(pr2), fused ? bs_res_stored<float, true> : bs_res_stored<float, false>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)vpart_, nb4, (const float2 *)sv, (const float2 *)t, (const float2 *)rh,
                            (void *const *)rtab_, n_, rpart_);
     else
-        launch_k(ctx_.prof_stamp(pr2), bs_res_stored<double>, dim3(nvb_), dim3(256), 0u, strm, S_,
-                           (const z64 *)vpart_, fused ? nb4 : 0, (const double2 *)sv, (const double2 *)t, (const double2 *)rh,
+        launch_k(ctx_.prof_stamp(pr2), fused ? bs_res_stored<double, true> : bs_res_stored<double, false>, dim3(nvb_), dim3(256), 0u, strm, S_,
+                           (const z64 *)vpart_, nb4, (const double2 *)sv, (const double2 *)t, (const double2 *)rh,
                            (void *const *)rtab_, n_, rpart_);
     ctx_.prof_stop(pr2, strm, SGN_K_SEED_UPDATE, 4.0 * eb * n_, 12.0 * n_);
     hipLaunchKernelGGL(bs_beta_kernel, dim3(1), dim3(256), 0, strm, S_, (const z64 *)rpart_, nvb_, hist_, maxiter_);
@@ -1852,18 +1837,22 @@ void BsBatch::launch_iteration(hipStream_t strm)
         if (!fused) hipLaunchKernelGGL(bs_alpha_batch, dim3(np), dim3(256), 0, strm, d);
         int pr = ctx_->prof_start(strm, SGN_K_SEED_UPDATE, true);
         if (f)
-            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
+            launch_k(ctx_->prof_stamp(pr), fused ? bs_sub_batch<float, true> : bs_sub_batch<float, false>, dim3(nvb_max_[ph], np),
+                     dim3(256), 0u, strm, d);
         else
-            launch_k(ctx_->prof_stamp(pr), bs_sub_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
+            launch_k(ctx_->prof_stamp(pr), fused ? bs_sub_batch<double, true> : bs_sub_batch<double, false>, dim3(nvb_max_[ph], np),
+                     dim3(256), 0u, strm, d);
         ctx_->prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * vbytes_[ph], 8.0 * nvec);
         stb_[ph][2].launch(strm);
         stb_[ph][3].launch(strm);
         if (!fused) hipLaunchKernelGGL(bs_omega_batch, dim3(np), dim3(256), 0, strm, d);
         pr = ctx_->prof_start(strm, SGN_K_SEED_UPDATE, true);
         if (f)
-            launch_k(ctx_->prof_stamp(pr), bs_res_batch<float>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
+            launch_k(ctx_->prof_stamp(pr), fused ? bs_res_batch<float, true> : bs_res_batch<float, false>, dim3(nvb_max_[ph], np),
+                     dim3(256), 0u, strm, d);
         else
-            launch_k(ctx_->prof_stamp(pr), bs_res_batch<double>, dim3(nvb_max_[ph], np), dim3(256), 0u, strm, d, fused);
+            launch_k(ctx_->prof_stamp(pr), fused ? bs_res_batch<double, true> : bs_res_batch<double, false>, dim3(nvb_max_[ph], np),
+                     dim3(256), 0u, strm, d);
         ctx_->prof_stop(pr, strm, SGN_K_SEED_UPDATE, 4.0 * vbytes_[ph], 12.0 * nvec);
         hipLaunchKernelGGL(bs_beta_batch, dim3(np), dim3(256), 0, strm, d, nvb_max_[ph]);
         pr = ctx_->prof_start(strm, SGN_K_SHIFT_UPDATE, true);

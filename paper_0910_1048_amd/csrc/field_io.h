@@ -178,25 +178,34 @@ __device__ __forceinline__ void load_link(const LT *__restrict__ U, int S, int n
     }
 }
 
-// Partial sum j of a dotting stencil (see pack_partials): `width` consecutive entries of STRIDE values.
-// All loads are issued before the first use.
-template <int STRIDE>
-__device__ __forceinline__ void partial_sum(const z64 *__restrict__ part, int j, int width, z64 (&s)[STRIDE])
+// A thread's share of a dotting stencil's partial sums (packed count; threads take strided sums): out[k] += the
+// k-th real value of an entry, entries of STRIDE values.  A sum of `width` entries is added up first, all its
+// loads issued before the first use.
+template <int STRIDE, int NV>
+__device__ __forceinline__ void add_partials(const z64 *__restrict__ part, int packed, double (&out)[NV])
 {
-    const z64 *p = part + (size_t)j * width * STRIDE;
+    const int n = partial_count(packed), width = partial_width(packed);
+    const double *p = reinterpret_cast<const double *>(part);
+    if (width == 1) {  // uniform
+        for (int i = threadIdx.x; i < n; i += blockDim.x)
 #pragma unroll
-    for (int k = 0; k < STRIDE; ++k) s[k] = p[k];
-    if (width == 1) return;  // uniform
-    z64 v[kMaxPartialWidth - 1][STRIDE];
+            for (int k = 0; k < NV; ++k) out[k] += p[(size_t)i * 2 * STRIDE + k];
+        return;
+    }
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        double v[kMaxPartialWidth][NV];
 #pragma unroll
-    for (int q = 1; q < kMaxPartialWidth; ++q)
+        for (int q = 0; q < kMaxPartialWidth; ++q)
 #pragma unroll
-        for (int k = 0; k < STRIDE; ++k) v[q - 1][k] = p[(q < width ? q : 0) * STRIDE + k];
+            for (int k = 0; k < NV; ++k) v[q][k] = p[((size_t)i * width + (q < width ? q : 0)) * 2 * STRIDE + k];
 #pragma unroll
-    for (int q = 1; q < kMaxPartialWidth; ++q)
+        for (int q = 1; q < kMaxPartialWidth; ++q)
 #pragma unroll
-        for (int k = 0; k < STRIDE; ++k)
-            if (q < width) s[k] = s[k] + v[q - 1][k];
+            for (int k = 0; k < NV; ++k)
+                if (q < width) v[0][k] += v[q][k];
+#pragma unroll
+        for (int k = 0; k < NV; ++k) out[k] += v[0][k];
+    }
 }
 
 // XCD-aware block order: consecutive hardware block ids are dealt round-robin

@@ -51,17 +51,10 @@ struct LzScalars {
 __device__ __forceinline__ z64 lz_alpha_body(const z64 *partials, int nblk, const LzScalars &S, int j, bool store)
 {
     const z64 sv = S.sv[j], tw = S.tw[j];
-    double re = 0.0, im = 0.0;
-    const int np = partial_count(nblk), width = partial_width(nblk);
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        z64 t[1];
-        partial_sum(partials, i, width, t);
-        re += t[0].r;
-        im += t[0].i;
-    }
+    double v[2] = {0.0, 0.0};
+    add_partials<1>(partials, nblk, v);
     __shared__ double lds[8];
     __shared__ z64 al;
-    double v[2] = {re, im};
     block_sum<2>(v, lds);
     if (threadIdx.x == 0) {
         const z64 d = {v[0], v[1]};

@@ -120,18 +120,11 @@ __global__ void __launch_bounds__(256) ms_alpha_kernel(const MsVec *vl, const in
     const MsVec &d = vl[list[blockIdx.x]];
     MsState *S = d.S;
     if (S->h.done) return;
-    double re = 0.0, im = 0.0;
-    const int np = partial_count(d.nst_part), width = partial_width(d.nst_part);
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        z64 t[1];
-        partial_sum(d.spart, i, width, t);
-        re += t[0].r;
-        im += t[0].i;
-    }
+    double v[2] = {0.0, 0.0};
+    add_partials<1>(d.spart, d.nst_part, v);
     __shared__ double lds[8];
     __shared__ z64 alpha_sh;
     __shared__ int bad_sh;
-    double v[2] = {re, im};
     block_sum<2>(v, lds);
     if (threadIdx.x == 0) {
         const z64 den = {v[0], v[1]};
