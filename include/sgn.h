@@ -153,9 +153,8 @@ sgn_status wilson_apply_noalloc(sgn_lattice lat, double mu, const void *in, void
  * (2 S N + L) bytes per site for N spinors of S bytes and links of L bytes
  * instead of N (2 S + L).  Each right-hand side's result is bitwise that of its
  * own wilson_apply.  mu (host) holds nrhs values; in/out (host arrays of device
- * pointers) must not alias each other.  The group's parameters live in device
- * memory owned by the lattice; a call with other fields or mu than the previous
- * one waits for the device to finish the earlier launches before replacing them. */
+ * pointers) must not alias each other.  The group's parameters travel with
+ * the launch: the call allocates nothing and does not wait for the device. */
 sgn_status wilson_apply_multi(sgn_lattice lat, int nrhs, const double *mu, const void *const *in,
                               void *const *out, sgn_prec p, unsigned flags, void *stream);
 

@@ -583,20 +583,19 @@ __device__ __forceinline__ void hop_pair_staged(cpx<R> (&acc)[12], const Stencil
     pin(acc);
 }
 
-// One block: B sites for each right-hand side in turn (kMulti: the P.nrhs right-hand sides
-// of P's group, all on P's lattice; else the single one, P.rhs[0]); the block's own spinors of
+// One block: B sites for each right-hand side in turn (kMulti: right-hand sides r0 .. r1 - 1
+// of P, all on P's lattice; else the single one, P.rhs[0]); the block's own spinors of
 // the current right-hand side are staged in LDS.  The single form indexes P.rhs only with
 // constants: P is then a kernel argument, and a runtime index into it would copy it to private
 // memory.
 template <typename R, typename LT, bool kEpi, bool kDot, bool kRegs, bool kMulti>
-__device__ __forceinline__ void staged_body(const StencilParams &P, const int bx)
+__device__ __forceinline__ void staged_body(const StencilParams &P, const int bx, const int r0 = 0, const int r1 = 1)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SpT<R> *lds = reinterpret_cast<SpT<R> *>(smem_raw);
     if (bx >= P.nblk_sites) {  // padding of the component arrays: keep it zero
         const int s = P.V + (bx - P.nblk_sites) * (int)blockDim.x + (int)threadIdx.x;
-        const int nr = kMulti ? P.nrhs : 1;
-        for (int r = 0; r < nr; ++r) {
+        for (int r = r0; r < r1; ++r) {
             const RhsParams &Q = P.rhs[kMulti ? r : 0];
             if (s < P.S) {
                 cpx<R> zero[12];
@@ -655,10 +654,9 @@ __device__ __forceinline__ void staged_body(const StencilParams &P, const int bx
     }
     SiteLinks<R, LT, kRegs> lk;
     if (valid) lk.load(P, s, c);
-    const int nr = kMulti ? P.nrhs : 1;
-    for (int r = 0; r < nr; ++r) {
+    for (int r = r0; r < r1; ++r) {
         const RhsParams &Q = P.rhs[kMulti ? r : 0];
-        if (r > 0) __syncthreads();  // the previous right-hand side's LDS reads are done
+        if (r > r0) __syncthreads();  // the previous right-hand side's LDS reads are done
         cpx<R> acc[12];
         if (valid) {
             load_spinor(static_cast<const SpT<R> *>(Q.in), P.S, s, acc);
@@ -717,7 +715,7 @@ __global__ void __launch_bounds__(kRegs ? kRegsMaxThreads : kStagedMaxThreads<R>
 {
     const StencilParams &P = plist[blockIdx.y];
     if ((int)blockIdx.x >= P.nblk_total) return;
-    staged_body<R, LT, kEpi, kDot, kRegs, true>(P, (int)blockIdx.x);
+    staged_body<R, LT, kEpi, kDot, kRegs, true>(P, (int)blockIdx.x, 0, P.nrhs);
 }
 
 // ---------------------------------------------------------------------------- split stencil
@@ -931,12 +929,11 @@ __device__ __forceinline__ void split_sum(cpx<R> (&acc)[2], const StencilParams 
 }
 
 template <typename R, typename LT, bool kEpi, bool kDot, bool kCanon, bool kMulti>
-__device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
+__device__ __forceinline__ void split_body(const StencilParams &P, const int bx, const int r0 = 0, const int r1 = 1)
 {
-    const int nr = kMulti ? P.nrhs : 1;
     if (bx >= P.nblk_sites) {  // padding of the component arrays (internal layout): keep it zero
         const int s = P.V + (bx - P.nblk_sites) * kSplitThreads + (int)threadIdx.x;
-        for (int r = 0; r < nr; ++r) {
+        for (int r = r0; r < r1; ++r) {
             const RhsParams &Q = P.rhs[kMulti ? r : 0];
             if (s < P.S) {
                 cpx<R> zero[12];
@@ -981,9 +978,9 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx)
         c[2] = q % P.L[2];
         c[3] = q / P.L[2];
     }
-    for (int r = 0; r < nr; ++r) {
+    for (int r = r0; r < r1; ++r) {
         const RhsParams &Q = P.rhs[kMulti ? r : 0];
-        if (r > 0) __syncthreads();  // the previous right-hand side's LDS reads are done
+        if (r > r0) __syncthreads();  // the previous right-hand side's LDS reads are done
         const bool mine = wave < 6;  // this wavefront finishes component pair `wave`
         // wavefront 7 takes the dot product: the 12 components of its sites in order, as the staged kernel does
         const bool dots = kDot && wave == 7;
@@ -1128,7 +1125,56 @@ __global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per
 {
     const StencilParams &P = plist[blockIdx.y];
     if ((int)blockIdx.x >= P.nblk_total) return;
-    split_body<R, LT, kEpi, kDot, false, true>(P, (int)blockIdx.x);
+    split_body<R, LT, kEpi, kDot, false, true>(P, (int)blockIdx.x, 0, P.nrhs);
+}
+
+// Several right-hand sides on one lattice without an epilogue, the parameters as a kernel argument: blockIdx.y
+// takes `per` of the P.nrhs right-hand sides.  P is read through the kernel-argument segment, because a
+// run-time index into a by-value argument would copy it to private memory.  With the parameters in device memory
+// each call with other fields than the last cost a wait for the device and a copy (8^4, 2 right-hand sides, fields
+// swapped between calls: 34 us a call, now 15; 16^3 x 32 FP16, 12: 128, now 91).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define SGN_KERNARG(P) (*(const StencilParams *)__builtin_amdgcn_kernarg_segment_ptr())
+#else
+#define SGN_KERNARG(P) (P)
+#endif
+template <typename R, typename LT, bool kRegs>
+__global__ void __launch_bounds__(kRegs ? kRegsMaxThreads : kStagedMaxThreads<R>)
+    stencil_staged_multi(StencilParams P, int per)
+{
+    const StencilParams &A = SGN_KERNARG(P);
+    if ((int)blockIdx.x >= A.nblk_total) return;
+    staged_body<R, LT, false, false, kRegs, true>(A, (int)blockIdx.x, (int)blockIdx.y * per,
+                                                  min(A.nrhs, ((int)blockIdx.y + 1) * per));
+}
+template <typename R, typename LT>
+__global__ void __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(kSplitWaves<R, false, true>)))
+    stencil_split_multi(StencilParams P, int per)
+{
+    const StencilParams &A = SGN_KERNARG(P);
+    if ((int)blockIdx.x >= A.nblk_total) return;
+    split_body<R, LT, false, false, false, true>(A, (int)blockIdx.x, (int)blockIdx.y * per,
+                                                 min(A.nrhs, ((int)blockIdx.y + 1) * per));
+}
+static_assert(offsetof(StencilParams, links) == 0 && sizeof(StencilParams) + 64 <= 4096,
+              "the first kernel argument, within the argument segment");
+
+template <typename R, typename LT>
+void launch_multi_kernarg(const StencilParams &P, int nblk, int threads, size_t lds, int per, bool split, bool regs,
+                          hipStream_t s, const LaunchStamp &ev)
+{
+    const dim3 g((nblk + 7) / 8 * 8, (P.nrhs + per - 1) / per);
+    if (split) {
+        launch_k(ev, stencil_split_multi<R, LT>, g, dim3(kSplitThreads), 0u, s, P, per);
+        return;
+    }
+    if constexpr (std::is_same<LT, __half2>::value) {
+        if (regs) {
+            launch_k(ev, stencil_staged_multi<R, LT, true>, g, dim3(threads), (uint32_t)lds, s, P, per);
+            return;
+        }
+    }
+    launch_k(ev, stencil_staged_multi<R, LT, false>, g, dim3(threads), (uint32_t)lds, s, P, per);
 }
 
 template <typename R, typename LT>
@@ -1470,21 +1516,75 @@ void launch_staged_batch(const StencilParams *dev, int count, int gx, int thread
 
 namespace {
 
+// Right-hand sides per block of a launch of nr of them over nblk blocks of sites: as many as leave the launch
+// 1024 blocks (four per CU), or as many blocks as groups of one would
+int rhs_per_block(int nr, int64_t nblk)
+{
+    const int64_t want = std::min<int64_t>(1024, nr * nblk);
+    int g = kMaxRhs;
+    while (g > 1 && (nr + g - 1) / g * nblk < want) --g;
+    return g;
+}
+
+// whether an application of several right-hand sides holds the links in registers: FP16 two-row links, unless
+// tuned otherwise or the environment asks for re-reads (SGN_MULTI_LINK_REGS=0)
+bool link_regs(const Lattice &lat, sgn_prec p)
+{
+    if (p != SGN_PREC_F32_H16 || lat.link_ne != 6) return false;
+    const char *e = std::getenv("SGN_MULTI_LINK_REGS");
+    return !(e && e[0] == '0') && lat.ctx->tuned_shape(lat.L, p, true).regs != 0;
+}
+
+// 2..16 right-hand sides without an epilogue in one launch; false if no kernel takes them together
+bool launch_rhs_block(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
+                      void *const *out, hipStream_t s)
+{
+    const std::vector<Epilogue> ep(nr);
+    const bool small = (double)nr * lat.V * (p == SGN_PREC_F64 ? 192 : 96) <= (double)kSplitMaxBytes;
+    const KernelPick pick = small && use_split(lat, p, true) ? kSplit : kStaged;
+    bool regs = pick == kStaged && link_regs(lat, p);
+    int cap = regs ? kRegsMaxThreads : 0;
+    if (regs && !lat.ctx->tuned.count({lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, 1})) {
+        // Two waves per SIMD hide little latency: below 1024 blocks half the block is faster where it fills its
+        // wavefronts as well (12 right-hand sides, 512 against 256 sites per block: 16^4 59 against 53 us,
+        // 16^3 x 32 98 against 91), and slower where it does not (20^4, 400 of 448 against 200 of 256 lanes: 141
+        // against 152 us; 12^3 x 24, 432 of 448 against 144 of 192: 40 against 56).
+        const StagedPlan full = staged_plan(lat, p, cap), half = staged_plan(lat, p, cap / 2);
+        if (full.ok && half.ok && full.nblk_sites < 1024 && half.B * full.threads >= full.B * half.threads) cap /= 2;
+    }
+    PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep.data(), cap, pick);
+    if (pick == kStaged && !ps.pl.ok) return false;
+    const int per = rhs_per_block(nr, ps.P.nblk_sites);
+    if (per < 2) regs = false;
+    const int prof = lat.ctx->prof_start(s, kclass(p), true);
+    const LaunchStamp ev = lat.ctx->prof_stamp(prof);
+    switch (p) {
+    case SGN_PREC_F64:
+        launch_multi_kernarg<double, double2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, per, ps.split, regs, s, ev);
+        break;
+    case SGN_PREC_F32:
+        launch_multi_kernarg<float, float2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, per, ps.split, regs, s, ev);
+        break;
+    default:
+        launch_multi_kernarg<float, __half2>(ps.P, ps.nblk, ps.pl.threads, ps.pl.lds, per, ps.split, regs, s, ev);
+        break;
+    }
+    SGN_HIP(hipGetLastError());
+    lat.ctx->prof_stop(prof, s, kclass(p), ps.bytes, ps.flops, false, ps.bytes_stored);
+    return true;
+}
+
 // canon: one right-hand side without an epilogue, in and out in the canonical layout (split kernel only)
 int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in, void *const *out,
                  const Epilogue *ep, hipStream_t s, bool canon)
 {
     const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep, 0, canon ? kSplit : kAuto);
-    if (nr > 1 && (ps.pl.ok || ps.split)) {
-        // several right-hand sides: the batched form, one group, parameters in device memory
-        // (the lattice's batch object: they are uploaded when they change, after the device has
-        // finished the launches that read the previous ones)
-        std::vector<StencilJob> jobs(nr);
-        for (int r = 0; r < nr; ++r) jobs[r] = StencilJob{&lat, op[r], in[r], out[r], ep[r]};
-        if (!lat.multi) lat.multi = std::make_shared<StencilBatch>();
-        lat.multi->prepare(jobs, p);
-        lat.multi->launch(s);
-        return ps.partials;
+    if (nr > 1) {
+        if (!ps.epi && !ps.dot && launch_rhs_block(lat, p, nr, op, in, out, s)) return ps.partials;
+        if (ps.split || ps.pl.ok) {
+            for (int r = 0; r < nr; ++r) launch_multi(lat, p, 1, op + r, in + r, out + r, ep + r, s, false);
+            return ps.partials;
+        }
     }
     // one launch unless the unstaged kernel runs several right-hand sides
     const int prof = lat.ctx->prof_start(s, kclass(p), ps.pl.ok || nr == 1);
@@ -1963,7 +2063,6 @@ extern "C" sgn_status sgn_tune_set(sgn_lattice l, sgn_prec p, int multi, int max
             const StagedPlan pl = staged_plan(lat, p, 0, max_sites, t_slices);
             SGN_REQUIRE(pl.ok && pl.T == t_slices, "sgn_tune_set: no staged block of this shape fits the lattice");
         }
-        // the parameters of earlier multi-RHS launches may still be read by the device
         SGN_HIP(hipSetDevice(lat.ctx->device));
         SGN_HIP(hipDeviceSynchronize());
         lat.ctx->tuned[{lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, multi ? 1 : 0}] =

@@ -184,8 +184,6 @@ struct Lattice {
     void *stage_in = nullptr, *stage_out = nullptr;
     size_t stage_bytes = 0;
     void ensure_stage(size_t bytes);
-    // parameters of multi-RHS launches on this lattice (wilson_apply_multi)
-    mutable std::shared_ptr<class StencilBatch> multi;
 };
 
 inline size_t spinor_bytes(int64_t S, sgn_prec p) { return (size_t)S * 12 * (p == SGN_PREC_F64 ? 16 : 8); }

@@ -86,3 +86,51 @@ def test_solves_have_the_same_bits_with_either_kernel(dims, prec, nprob):
     assert its == its2
     for a, c in zip(x, y):
         assert torch.equal(a, c)
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32, sgn.F32_H16])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (5, 13, 2, 2), (8, 8, 8, 8), (15, 13, 4, 6), (16, 16, 16, 16), (12, 12, 12, 24)])
+@pytest.mark.parametrize("nrhs", [2, 5, 17])
+def test_several_right_hand_sides_swap_their_fields(dims, prec, nrhs):
+    """Every right-hand side as if alone, with other fields at each call, eager and in a captured graph."""
+    U = synth.gauge_field(dims, 0.4, 7)
+    lat = sgn.Lattice(ctx(), dev(U), dims, 0.2)
+    mus = [0.1 * (j % 4) - 0.1 for j in range(nrhs)]
+    nb = lat.spinor_bytes(prec)
+    x, y, z = ([torch.empty(nb, dtype=torch.uint8, device="cuda") for _ in range(nrhs)] for _ in range(3))
+    for j in range(nrhs):
+        sgn.sgn_spinor_pack(lat, dev(synth.gaussian_source(dims, 3 + j).astype(CDT[prec])), x[j], prec)
+    keep = [t.clone() for t in x]
+
+    def field(t):  # the written bytes (padding included) as numbers
+        return host(t.view(torch.float64 if prec == sgn.F64 else torch.float32))
+
+    want = []
+    for j in range(nrhs):
+        t, u = torch.empty_like(x[j]), torch.empty_like(x[j])
+        sgn.wilson_apply(lat, mus[j], x[j], t, prec, sgn.INTERNAL_LAYOUT)
+        sgn.wilson_apply(lat, mus[j], t, u, prec, sgn.INTERNAL_LAYOUT)
+        want.append(field(u))
+
+    def twice():
+        sgn.wilson_apply_multi(lat, mus, x, y, prec)
+        sgn.wilson_apply_multi(lat, mus, y, z, prec)
+
+    def check():
+        torch.cuda.synchronize()
+        for j in range(nrhs):
+            got = field(z[j])
+            assert np.linalg.norm(got - want[j]) <= TOL[prec] * np.linalg.norm(want[j]), j
+
+    twice()
+    check()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        twice()
+    for _ in range(3):
+        for j in range(nrhs):
+            z[j].zero_()
+            y[j].zero_()
+            x[j].copy_(keep[j])
+        g.replay()
+        check()
