@@ -480,12 +480,22 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
             Epilogue ep;
             ep.w = f32 ? w32.p : Wj(j);
             ep.partials = part;
-            const int nb1 = dslash_launch(lat, sp, opA, f32 ? v32.p : Vj(j), f32 ? u32.p : u.p, ep, s);
+            const void *av = f32 ? v32.p : Vj(j), *aw = f32 ? w32.p : Wj(j);
+            void *ou = f32 ? u32.p : u.p, *oz = f32 ? z32.p : z.p;
+            int nb1;
+            if (j + 1 == last) {
+                nb1 = dslash_launch(lat, sp, opA, av, ou, ep, s);
+            } else {  // and z = A^H wh_j
+                if (!two_pass) basis.ensure(j + 1);
+                const OpSpec op2[2] = {opA, opAh};
+                const void *in2[2] = {av, aw};
+                void *out2[2] = {ou, oz};
+                const Epilogue ep2[2] = {ep, Epilogue{}};
+                nb1 = dslash_launch_pair(lat, sp, op2, in2, out2, ep2, s);
+            }
             const int na = j + 1 < last && partial_count(nb1) * partial_width(nb1) <= kLzFusedPartials ? nb1 : 0;
             if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s, part, nb1, S, j);
             if (j + 1 == last) return;
-            if (!two_pass) basis.ensure(j + 1);
-            dslash_launch(lat, sp, opAh, f32 ? w32.p : Wj(j), f32 ? z32.p : z.p, Epilogue{}, s);
             void *vn = Vj(j + 1);
             const double2 *vjm = j > 0 ? reinterpret_cast<const double2 *>(Vj(j - 1)) : nullptr;
             const double2 *wjm = j > 0 ? reinterpret_cast<const double2 *>(Wj(j - 1)) : nullptr;
@@ -832,18 +842,32 @@ void QmrSolve::step(int j)
     const bool f32 = f32_;
     PooledBasis &basis = *basis_;
     char *tmp = static_cast<char *>(tmp_->p), *u = static_cast<char *>(u_->p), *z = static_cast<char *>(z_->p);
-    dslash_launch(lat_, sp_, opA_, f32 ? v32_->p : basis[j], f32 ? t32_->p : tmp, Epilogue{}, s_);
+    const OpSpec op2[2] = {opA_, opAh_};
+    const void *av = f32 ? v32_->p : basis[j], *aw = f32 ? w32_->p : Wj(j);
+    void *ou = f32 ? u32_->p : u, *oz = f32 ? z32_->p : z;
     Epilogue ep;  // u = c^2 H (H vh_j), partials of wh_j^H u
     ep.a = c2_;
-    ep.w = f32 ? w32_->p : Wj(j);
+    ep.w = aw;
     ep.partials = part_;
-    const int nb1 = dslash_launch(lat_, sp_, opA_, f32 ? t32_->p : tmp, f32 ? u32_->p : u, ep, s_);
-    const int na = partial_count(nb1) * partial_width(nb1) <= kLzFusedPartials ? nb1 : 0;
-    if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s_, part_, nb1, S_, j);
-    dslash_launch(lat_, sp_, opAh_, f32 ? w32_->p : Wj(j), f32 ? t32_->p : tmp, Epilogue{}, s_);
     Epilogue ez;  // z = c^2 H^H (H^H wh_j)
     ez.a = c2_;
-    dslash_launch(lat_, sp_, opAh_, f32 ? t32_->p : tmp, f32 ? z32_->p : z, ez, s_);
+    void *t = f32 ? t32_->p : tmp;
+    int nb1;
+    if (dslash_pairs(lat_, sp_)) {
+        // the slot of vh_{j+1}, written by the update below, holds H^H wh_j until then
+        const void *in1[2] = {av, aw}, *in2[2] = {t, basis[j + 1]};
+        void *out1[2] = {t, basis[j + 1]}, *out2[2] = {ou, oz};
+        const Epilogue ep1[2], ep2[2] = {ep, ez};
+        dslash_launch_pair(lat_, sp_, op2, in1, out1, ep1, s_);
+        nb1 = dslash_launch_pair(lat_, sp_, op2, in2, out2, ep2, s_);
+    } else {  // each temporary is read while the caches hold it
+        dslash_launch(lat_, sp_, opA_, av, t, Epilogue{}, s_);
+        nb1 = dslash_launch(lat_, sp_, opA_, t, ou, ep, s_);
+        dslash_launch(lat_, sp_, opAh_, aw, t, Epilogue{}, s_);
+        dslash_launch(lat_, sp_, opAh_, t, oz, ez, s_);
+    }
+    const int na = partial_count(nb1) * partial_width(nb1) <= kLzFusedPartials ? nb1 : 0;
+    if (!na) hipLaunchKernelGGL(lz_alpha_kernel, dim3(1), dim3(256), 0, s_, part_, nb1, S_, j);
     const double2 *vjm = j > 0 ? static_cast<const double2 *>(basis[j - 1]) : nullptr;
     const double2 *wjm = j > 0 ? reinterpret_cast<const double2 *>(Wj(j - 1)) : nullptr;
     const int pr = ctx_.prof_start(s_, SGN_K_SEED_UPDATE, true);

@@ -670,6 +670,7 @@ class MultishiftBatch {
     std::vector<MsVec> hvec_;
     std::vector<int> lists_[3][2];  // active problems per phase and form (0 stored basis, 1 per-shift)
     StencilBatch stb_[3][4];        // per phase, the four stencil steps of an iteration
+    std::vector<StencilJob> pairs_[3];  // the four of a single problem where they run as two launches
     bool dirty_ = true;             // lists and stencil batches need rebuilding
     bool dirty_vec_ = false;        // only the descriptors changed
     std::map<size_t, size_t> pool_next_;  // next unused pooled slot per vector size in this call
@@ -681,6 +682,7 @@ class MultishiftBatch {
     void fill_vec(int k);
     void iterate(int count);               // launches + host bookkeeping of count iterations
     void launch_iterations(int count, hipStream_t strm);
+    void launch_pairs(int ph, hipStream_t strm);
     void drop_graph()
     {
         if (gexec_) SGN_HIP(hipGraphExecDestroy(gexec_));
@@ -955,6 +957,10 @@ void MultishiftBatch::rebuild()
         job_owner[p.phase].push_back(k);
     }
     for (int ph = 0; ph < 3; ++ph) {
+        // one problem on a small lattice: A p with A^H ptilde, the dot product's partials as the batch leaves them
+        pairs_[ph].clear();
+        if (jobs[ph][0].size() == 1 && dslash_pairs(*jobs[ph][0][0].lat, prec_of(ph)))
+            for (int st = 0; st < 4; ++st) pairs_[ph].push_back(jobs[ph][st][0]);
         for (int st = 0; st < 4; ++st) stb_[ph][st].prepare(jobs[ph][st], prec_of(ph));
         for (size_t j = 0; j < job_owner[ph].size(); ++j) hvec_[job_owner[ph][j]].nst_part = stb_[ph][1].blocks(j);
     }
@@ -983,6 +989,18 @@ void MultishiftBatch::iterate(int count)
         }
 }
 
+void MultishiftBatch::launch_pairs(int ph, hipStream_t strm)
+{
+    for (int st = 0; st < 2; ++st) {
+        const StencilJob &a = pairs_[ph][st], &b = pairs_[ph][st + 2];
+        const OpSpec op[2] = {a.op, b.op};
+        const void *in[2] = {a.in, b.in};
+        void *out[2] = {a.out, b.out};
+        const Epilogue ep[2] = {a.ep, b.ep};
+        dslash_launch_pair(*a.lat, prec_of(ph), op, in, out, ep, strm);
+    }
+}
+
 void MultishiftBatch::launch_iterations(int count, hipStream_t strm)
 {
     const int np = (int)pr_.size();
@@ -990,7 +1008,10 @@ void MultishiftBatch::launch_iterations(int count, hipStream_t strm)
         for (int ph = 0; ph < 3; ++ph) {
             const int nb = (int)lists_[ph][0].size(), ne = (int)lists_[ph][1].size();
             if (nb + ne == 0) continue;
-            for (int st = 0; st < 4; ++st) stb_[ph][st].launch(strm);
+            if (pairs_[ph].empty())
+                for (int st = 0; st < 4; ++st) stb_[ph][st].launch(strm);
+            else
+                launch_pairs(ph, strm);
             const int *lb = dlist_ + (size_t)(2 * ph) * np, *le = dlist_ + (size_t)(2 * ph + 1) * np;
             const bool lo = ph >= 1;
             if (nb) hipLaunchKernelGGL(ms_alpha_kernel, dim3(nb), dim3(256), 0, strm, dvec_, lb);

@@ -232,6 +232,11 @@ __host__ __device__ inline int partial_width(int p) { return (p >> 24) + 1; }
 // its own operator (mu, gamma5 flags), input, output and epilogue.
 int dslash_launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
                         void *const *out, const Epilogue *ep, hipStream_t s);
+// two applications on one lattice of which neither reads what the other writes, in one launch where dslash_pairs
+// (small lattices on the split kernel), else one after the other; returns the partial count of the first
+bool dslash_pairs(const Lattice &lat, sgn_prec p);
+int dslash_launch_pair(const Lattice &lat, sgn_prec p, const OpSpec *op, const void *const *in, void *const *out,
+                       const Epilogue *ep, hipStream_t s);
 int dslash_launch(const Lattice &lat, sgn_prec p, const OpSpec &op, const void *in, void *out,
                   const Epilogue &ep, hipStream_t s);
 // The operator on canonical-layout fields in one launch, where a kernel takes them; false (nothing

@@ -134,3 +134,31 @@ def test_several_right_hand_sides_swap_their_fields(dims, prec, nrhs):
             x[j].copy_(keep[j])
         g.replay()
         check()
+
+
+# one problem on a lattice of the split kernel runs its two independent applications in one launch: against two
+# launches of a pinned staged shape, at the smallest sizes and on either side of the FP64 limit
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (8, 8, 8, 2), (5, 13, 2, 4), (16, 16, 16, 12), (16, 16, 8, 25)])
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32_H16])
+def test_paired_applications_of_the_two_sided_solvers(dims, prec):
+    U = dev(synth.gauge_field(dims, 0.2, 7))
+    b = dev(synth.gaussian_source(dims, 3).ravel())
+    rf = sgn.sgn_rational_neuberger(6, 0.15, 2.6)
+    c = sgn.Context(0)
+    lat = sgn.Lattice(c, U, dims, 0.12)
+
+    def results():
+        xs = [torch.empty_like(b) for _ in range(3)]
+        sgn.sign_lanczos_2sided(lat, 0.1, b, xs[0], k=12, prec=prec)
+        sgn.multishift_solve(sgn.Problem(lat, 0.1, b, xs[1]), rf, tol=1e-9, prec=prec)
+        sgn.multishift_qmr(sgn.Problem(lat, 0.1, b, xs[2]), rf, tol=1e-9, prec=prec)
+        return [host(x) for x in xs]
+
+    paired = results()
+    for p in (sgn.F64, sgn.F32, sgn.F32_H16):
+        sgn.sgn_tune_set(lat, p, False, 0, 1)
+    single = results()
+    # Lanczos of 12 steps: rounding (a shadow pairing off by an operator would be an error of order one); the
+    # solvers: their tolerance, times ten for its being a residual's
+    for x, y, tol in zip(paired, single, (1e-11 if prec == sgn.F64 else 1e-2, 1e-8, 1e-8)):
+        assert np.all(np.isfinite(x)) and np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
