@@ -134,47 +134,71 @@ __global__ void __launch_bounds__(256) su3_check_kernel(const double2 *__restric
     if (threadIdx.x == 0) blockmax[blockIdx.x] = red[0];
 }
 
-// internal layouts: padding sites (V <= s < S) are written as zeros
-__global__ void pack64(const double2 *__restrict__ c, double2 *__restrict__ o, int V, int S)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) o[(size_t)k * S + s] = s < V ? c[(size_t)s * 12 + k] : make_double2(0.0, 0.0);
-}
+// Canonical <-> internal layout without a rotation: a transpose of 16-byte units, 12 (FP64) or 6 (FP32) a site.
+// Memory-bound; a lane per site would touch one unit of a 96- or 192-byte site per load, 64 lines a wavefront,
+// which is what the address units and not memory then bound, so 768 units a block go through LDS and both sides
+// are read and written in order (rows of 13 units for 12: no bank conflicts).  Repeated conversions, a lane per
+// site before and now: 24^3 x 48 FP32, 127 MB, pack 24.6 -> 20.8 us, unpack 27.2 -> 20.2 (6.3 TB/s); FP64, 255 MB,
+// 60.4 -> 39.5 and 49.1 -> 37.9; 16^3 x 32 FP32, 25 MB, 7.1 -> 6.9 and 8.4 -> 6.3 (from then on the launch).
+// The canonical side may be aligned to 8 bytes only.
+typedef unsigned int unit16 __attribute__((ext_vector_type(4)));
+typedef unit16 unit16_a8 __attribute__((aligned(8)));
+constexpr int kPackUnits = 768, kPackThreads = 256;
+template <int N>
+constexpr int kPackRow = N == 12 ? 13 : N;
 
-__global__ void unpack64(const double2 *__restrict__ o, double2 *__restrict__ c, int V, int S)
+// padding sites (V <= s < S) are written as zeros
+template <int N>
+__global__ void __launch_bounds__(kPackThreads) pack_units(const unit16_a8 *__restrict__ c, unit16 *__restrict__ o,
+                                                           int V, int S)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
+    constexpr int B = kPackUnits / N, LD = kPackRow<N>;
+    __shared__ unit16 lds[B * LD];
+    const int s0 = blockIdx.x * B, n = min(B, V - s0) * N;
+    unit16 v[kPackUnits / kPackThreads];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) c[(size_t)s * 12 + k] = o[(size_t)k * S + s];
-}
-
-__global__ void pack32(const float2 *__restrict__ c, float4 *__restrict__ o, int V, int S)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads;
+        v[q] = unit16{0, 0, 0, 0};
+        if (e < n) v[q] = c[(size_t)s0 * N + e];
+    }
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        if (s >= V) {
-            o[(size_t)k * S + s] = make_float4(0.f, 0.f, 0.f, 0.f);
-            continue;
-        }
-        float2 a = c[(size_t)s * 12 + 2 * k], b = c[(size_t)s * 12 + 2 * k + 1];
-        o[(size_t)k * S + s] = make_float4(a.x, a.y, b.x, b.y);
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads;
+        lds[e / N * LD + e % N] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads, k = e / B, j = e % B;
+        if (s0 + j < S) o[(size_t)k * S + s0 + j] = lds[j * LD + k];
     }
 }
 
-__global__ void unpack32(const float4 *__restrict__ o, float2 *__restrict__ c, int V, int S)
+template <int N>
+__global__ void __launch_bounds__(kPackThreads) unpack_units(const unit16 *__restrict__ o, unit16_a8 *__restrict__ c,
+                                                             int V, int S)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
+    constexpr int B = kPackUnits / N, LD = kPackRow<N>;
+    __shared__ unit16 lds[B * LD];
+    const int s0 = blockIdx.x * B, n = min(B, V - s0) * N;
+    unit16 v[kPackUnits / kPackThreads];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        float4 t = o[(size_t)k * S + s];
-        c[(size_t)s * 12 + 2 * k] = make_float2(t.x, t.y);
-        c[(size_t)s * 12 + 2 * k + 1] = make_float2(t.z, t.w);
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads, k = e / B, j = e % B;
+        v[q] = unit16{0, 0, 0, 0};
+        if (s0 + j < V) v[q] = o[(size_t)k * S + s0 + j];
+    }
+#pragma unroll
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads, k = e / B, j = e % B;
+        lds[j * LD + k] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPackUnits / kPackThreads; ++q) {
+        const int e = threadIdx.x + q * kPackThreads;
+        if (e < n) c[(size_t)s0 * N + e] = lds[e / N * LD + e % N];
     }
 }
 
@@ -243,72 +267,98 @@ __global__ void tg_links_kernel(const double2 *__restrict__ canon, const double2
         }
 }
 
-// spinor components (spin 4 x colour 3) rotated in colour: G psi (kAdj false) or G^H psi
-template <bool kAdj>
-__device__ inline void rotate12(const double2 *__restrict__ G, int s, z64 v[12])
+// The internal layouts of a temporal-gauge lattice hold G psi.  One block takes 64 sites: their components and
+// rotations are brought into LDS in memory order, wavefront sp rotates spin sp of the 64 sites in FP64 and in
+// place (pack: G psi, unpack: G^H psi), and the result goes out in memory order.  Memory-bound: G is 144 bytes a
+// site beside the spinor's 192 (FP32, in and out); 24^3 x 48 FP32, 223 MB: pack 50.1 -> 36.6 us, unpack
+// 37.2 -> 35.7 (6.2 TB/s; with cold caches 54 -> 39 and 50 -> 42); FP64, 350 MB: 82.6 -> 68.8 and 75.4 -> 65.0.
+constexpr int kTgSites = 64, kTgThreads = 256, kTgRow = 13;  // rows of 12 components, padded against bank conflicts
+
+template <bool kAdj, typename T>
+__device__ __forceinline__ void tg_rotate(T *__restrict__ cl, const double2 *__restrict__ gl)
 {
-    z64 g[9];
-    for (int e = 0; e < 9; ++e) g[e] = ldc(G + (size_t)s * 9 + e);
-    for (int sp = 0; sp < 4; ++sp) {
-        const z64 a0 = v[3 * sp], a1 = v[3 * sp + 1], a2 = v[3 * sp + 2];
-        for (int i = 0; i < 3; ++i)
-            v[3 * sp + i] = kAdj ? cmulc(g[i], a0) + cmulc(g[3 + i], a1) + cmulc(g[6 + i], a2)
-                                 : g[3 * i] * a0 + g[3 * i + 1] * a1 + g[3 * i + 2] * a2;
+    const int j = threadIdx.x % kTgSites, sp = threadIdx.x / kTgSites;
+    z64 g[9], a[3], r[3];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) g[e] = ldc(gl + j * 9 + e);
+    T *x = cl + j * kTgRow + 3 * sp;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) a[i] = {(double)x[i].x, (double)x[i].y};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        r[i] = kAdj ? cmulc(g[i], a[0]) + cmulc(g[3 + i], a[1]) + cmulc(g[6 + i], a[2])
+                    : g[3 * i] * a[0] + g[3 * i + 1] * a[1] + g[3 * i + 2] * a[2];
+    }
+    using C = decltype(x[0].x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        x[i].x = static_cast<std::remove_reference_t<C>>(r[i].r);
+        x[i].y = static_cast<std::remove_reference_t<C>>(r[i].i);
     }
 }
 
-// the internal layouts of a temporal-gauge lattice hold G psi; the rotation is done in FP64
-__global__ void pack64g(const double2 *__restrict__ c, const double2 *__restrict__ G, double2 *__restrict__ o, int V,
-                        int S)
+__device__ __forceinline__ void tg_load_gauge(const double2 *__restrict__ G, int s0, int nsites, double2 *gl)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    z64 v[12];
-    for (int k = 0; k < 12; ++k) v[k] = s < V ? ldc(c + (size_t)s * 12 + k) : z64{0.0, 0.0};
-    if (s < V) rotate12<false>(G, s, v);
-    for (int k = 0; k < 12; ++k) stc(o + (size_t)k * S + s, v[k]);
+    for (int e = threadIdx.x; e < kTgSites * 9; e += kTgThreads)
+        gl[e] = e < nsites * 9 ? G[(size_t)s0 * 9 + e] : make_double2(0.0, 0.0);
 }
 
-__global__ void unpack64g(const double2 *__restrict__ o, const double2 *__restrict__ G, double2 *__restrict__ c, int V,
-                          int S)
+// a unit of the internal layouts: components k and k + 1 (FP32), or k (FP64)
+__device__ __forceinline__ void tg_put(float2 *x, float4 u)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    z64 v[12];
-    for (int k = 0; k < 12; ++k) v[k] = ldc(o + (size_t)k * S + s);
-    rotate12<true>(G, s, v);
-    for (int k = 0; k < 12; ++k) stc(c + (size_t)s * 12 + k, v[k]);
+    x[0] = make_float2(u.x, u.y);
+    x[1] = make_float2(u.z, u.w);
 }
+__device__ __forceinline__ void tg_put(double2 *x, double2 u) { x[0] = u; }
+__device__ __forceinline__ void tg_get(const float2 *x, float4 &u) { u = make_float4(x[0].x, x[0].y, x[1].x, x[1].y); }
+__device__ __forceinline__ void tg_get(const double2 *x, double2 &u) { u = x[0]; }
 
-__global__ void pack32g(const float2 *__restrict__ c, const double2 *__restrict__ G, float4 *__restrict__ o, int V,
-                        int S)
+template <typename T, typename U>
+__global__ void __launch_bounds__(kTgThreads) pack_gauge(const T *__restrict__ c, const double2 *__restrict__ G,
+                                                         U *__restrict__ o, int V, int S)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    z64 v[12];
-    for (int k = 0; k < 12; ++k) {
-        const float2 a = s < V ? c[(size_t)s * 12 + k] : make_float2(0.f, 0.f);
-        v[k] = {(double)a.x, (double)a.y};
+    constexpr int NU = sizeof(T) * 12 / sizeof(U), W = 12 / NU;
+    __shared__ T cl[kTgSites * kTgRow];
+    __shared__ double2 gl[kTgSites * 9];
+    const int s0 = blockIdx.x * kTgSites, ns = min(kTgSites, V - s0);  // ns <= 0: padding only
+#pragma unroll
+    for (int q = 0; q < kTgSites * 12 / kTgThreads; ++q) {
+        const int e = threadIdx.x + q * kTgThreads;
+        cl[e / 12 * kTgRow + e % 12] = e < ns * 12 ? c[(size_t)s0 * 12 + e] : T{};
     }
-    if (s < V) rotate12<false>(G, s, v);
-    for (int k = 0; k < 6; ++k)
-        o[(size_t)k * S + s] = make_float4((float)v[2 * k].r, (float)v[2 * k].i, (float)v[2 * k + 1].r,
-                                           (float)v[2 * k + 1].i);
+    tg_load_gauge(G, s0, ns, gl);
+    __syncthreads();
+    tg_rotate<false>(cl, gl);
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTgSites * NU; e += kTgThreads) {
+        const int k = e / kTgSites, j = e % kTgSites;
+        U u;
+        tg_get(cl + j * kTgRow + k * W, u);
+        if (s0 + j < S) o[(size_t)k * S + s0 + j] = u;
+    }
 }
 
-__global__ void unpack32g(const float4 *__restrict__ o, const double2 *__restrict__ G, float2 *__restrict__ c, int V,
-                          int S)
+template <typename T, typename U>
+__global__ void __launch_bounds__(kTgThreads) unpack_gauge(const U *__restrict__ o, const double2 *__restrict__ G,
+                                                           T *__restrict__ c, int V, int S)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    z64 v[12];
-    for (int k = 0; k < 6; ++k) {
-        const float4 t = o[(size_t)k * S + s];
-        v[2 * k] = {(double)t.x, (double)t.y};
-        v[2 * k + 1] = {(double)t.z, (double)t.w};
+    constexpr int NU = sizeof(T) * 12 / sizeof(U), W = 12 / NU;
+    __shared__ T cl[kTgSites * kTgRow];
+    __shared__ double2 gl[kTgSites * 9];
+    const int s0 = blockIdx.x * kTgSites, ns = min(kTgSites, V - s0);
+    for (int e = threadIdx.x; e < kTgSites * NU; e += kTgThreads) {
+        const int k = e / kTgSites, j = e % kTgSites;
+        tg_put(cl + j * kTgRow + k * W, j < ns ? o[(size_t)k * S + s0 + j] : U{});
     }
-    rotate12<true>(G, s, v);
-    for (int k = 0; k < 12; ++k) c[(size_t)s * 12 + k] = make_float2((float)v[k].r, (float)v[k].i);
+    tg_load_gauge(G, s0, ns, gl);
+    __syncthreads();
+    tg_rotate<true>(cl, gl);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTgSites * 12 / kTgThreads; ++q) {
+        const int e = threadIdx.x + q * kTgThreads;
+        if (e < ns * 12) c[(size_t)s0 * 12 + e] = cl[e / 12 * kTgRow + e % 12];
+    }
 }
 
 }  // namespace
@@ -316,32 +366,38 @@ __global__ void unpack32g(const float4 *__restrict__ o, const double2 *__restric
 void pack_spinor(const Lattice &lat, const void *canon, void *internal, sgn_prec p, hipStream_t s)
 {
     const int V = (int)lat.V, S = (int)lat.S;
-    dim3 g((S + 255) / 256), b(256);
     const double2 *G = static_cast<const double2 *>(lat.gauge);
-    if (p == SGN_PREC_F64 && G)
-        hipLaunchKernelGGL(pack64g, g, b, 0, s, (const double2 *)canon, G, (double2 *)internal, V, S);
+    const bool f64 = p == SGN_PREC_F64;
+    const int B = G ? kTgSites : kPackUnits / (f64 ? 12 : 6);
+    dim3 g((S + B - 1) / B), b(G ? kTgThreads : kPackThreads);
+    if (f64 && G)
+        hipLaunchKernelGGL((pack_gauge<double2, double2>), g, b, 0, s, (const double2 *)canon, G, (double2 *)internal, V,
+                           S);
     else if (G)
-        hipLaunchKernelGGL(pack32g, g, b, 0, s, (const float2 *)canon, G, (float4 *)internal, V, S);
-    else if (p == SGN_PREC_F64)
-        hipLaunchKernelGGL(pack64, g, b, 0, s, (const double2 *)canon, (double2 *)internal, V, S);
+        hipLaunchKernelGGL((pack_gauge<float2, float4>), g, b, 0, s, (const float2 *)canon, G, (float4 *)internal, V, S);
+    else if (f64)
+        hipLaunchKernelGGL(pack_units<12>, g, b, 0, s, (const unit16_a8 *)canon, (unit16 *)internal, V, S);
     else
-        hipLaunchKernelGGL(pack32, g, b, 0, s, (const float2 *)canon, (float4 *)internal, V, S);
+        hipLaunchKernelGGL(pack_units<6>, g, b, 0, s, (const unit16_a8 *)canon, (unit16 *)internal, V, S);
     SGN_HIP(hipGetLastError());
 }
 
 void unpack_spinor(const Lattice &lat, const void *internal, void *canon, sgn_prec p, hipStream_t s)
 {
     const int V = (int)lat.V, S = (int)lat.S;
-    dim3 g((V + 255) / 256), b(256);
     const double2 *G = static_cast<const double2 *>(lat.gauge);
-    if (p == SGN_PREC_F64 && G)
-        hipLaunchKernelGGL(unpack64g, g, b, 0, s, (const double2 *)internal, G, (double2 *)canon, V, S);
+    const bool f64 = p == SGN_PREC_F64;
+    const int B = G ? kTgSites : kPackUnits / (f64 ? 12 : 6);
+    dim3 g((V + B - 1) / B), b(G ? kTgThreads : kPackThreads);
+    if (f64 && G)
+        hipLaunchKernelGGL((unpack_gauge<double2, double2>), g, b, 0, s, (const double2 *)internal, G, (double2 *)canon, V,
+                           S);
     else if (G)
-        hipLaunchKernelGGL(unpack32g, g, b, 0, s, (const float4 *)internal, G, (float2 *)canon, V, S);
-    else if (p == SGN_PREC_F64)
-        hipLaunchKernelGGL(unpack64, g, b, 0, s, (const double2 *)internal, (double2 *)canon, V, S);
+        hipLaunchKernelGGL((unpack_gauge<float2, float4>), g, b, 0, s, (const float4 *)internal, G, (float2 *)canon, V, S);
+    else if (f64)
+        hipLaunchKernelGGL(unpack_units<12>, g, b, 0, s, (const unit16 *)internal, (unit16_a8 *)canon, V, S);
     else
-        hipLaunchKernelGGL(unpack32, g, b, 0, s, (const float4 *)internal, (float2 *)canon, V, S);
+        hipLaunchKernelGGL(unpack_units<6>, g, b, 0, s, (const unit16 *)internal, (unit16_a8 *)canon, V, S);
     SGN_HIP(hipGetLastError());
 }
 

@@ -162,3 +162,40 @@ def test_paired_applications_of_the_two_sided_solvers(dims, prec):
     # solvers: their tolerance, times ten for its being a residual's
     for x, y, tol in zip(paired, single, (1e-11 if prec == sgn.F64 else 1e-2, 1e-8, 1e-8)):
         assert np.all(np.isfinite(x)) and np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (3, 3, 7, 2), (4, 4, 4, 2), (5, 13, 2, 2), (8, 8, 8, 8), (5, 7, 3, 11)])
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32])
+def test_layout_conversions_at_the_edges_of_their_blocks(dims, prec):
+    """Bytes are only moved without a gauge; with the temporal gauge packing is undone by unpacking."""
+    V = int(np.prod(dims))
+    U = dev(synth.gauge_field(dims, 0.4, 7))
+    b = synth.gaussian_source(dims, 3).astype(CDT[prec]).reshape(V, 12)
+    room = torch.empty(12 * V + 1, dtype=torch.complex128 if prec == sgn.F64 else torch.complex64, device="cuda")
+    for off in (0, 1):  # the canonical field may start at any element
+        bd = room[off:off + 12 * V]
+        bd.copy_(dev(b.ravel()))
+        for flags in (0, sgn.LINKS_TEMPORAL_GAUGE):
+            lat = sgn.Lattice(ctx(), U, dims, 0.2, prec_mask=flags)
+            nb = lat.spinor_bytes(prec)
+            S = nb // (12 * b.itemsize)
+            x = torch.full((nb,), 255, dtype=torch.uint8, device="cuda")
+            sgn.sgn_spinor_pack(lat, bd, x, prec)
+            w = 1 if prec == sgn.F64 else 2  # components per unit
+            internal = host(x).view(CDT[prec]).reshape(12 // w, S, w)
+            assert not internal[:, V:].any()
+            got = internal[:, :V].transpose(1, 0, 2).reshape(V, 12)
+            back = torch.zeros_like(room)
+            sgn.sgn_spinor_unpack(lat, x, back[off:off + 12 * V], prec)
+            back = host(back)
+            assert back[12 * V if off == 0 else 0] == 0  # nothing beside the field
+            back = back[off:off + 12 * V].reshape(V, 12)
+            if flags == 0:
+                assert np.array_equal(got, b) and np.array_equal(back, b)
+            else:  # a colour rotation in FP64: lengths are kept, and the first time slice itself
+                # two roundings of the stored values, and the unitarity of a product of L_t links
+                tol = 1e-13 if prec == sgn.F64 else 4e-7
+                v3 = V // dims[3]
+                assert np.array_equal(got[:v3], b[:v3])
+                assert np.allclose(np.linalg.norm(got, axis=1), np.linalg.norm(b, axis=1), rtol=tol)
+                assert np.linalg.norm(back - b) <= tol * np.linalg.norm(b)
