@@ -533,6 +533,9 @@ __device__ __forceinline__ void stz_nt(float2 *p, int64_t e, z64 v)
 // All of them are bound by latency: the loads (the flags, the partials and, in the thread of each shift, that
 // shift's state) are issued before the first use.
 constexpr int kBsFusedPartials = 1024;
+// A batch's blocks do not all fit the chip at once, and each adds the partials again: 24 problems on 8^4, 12^4 and
+// 16^4 (25,700 blocks with work), FP32: s and r' updates 47 + 58 us fused, 37 + 41 and two launches apart.
+constexpr int kBsFusedBlocks = 8192;
 static_assert(kBsShifts <= 256, "one thread per shift in the 256-thread scalar kernels");
 
 // alpha = rho / r^^H v from the dotting stencil's partials; the BiCG factors zeta_next (writer: this block
@@ -595,6 +598,8 @@ __device__ __forceinline__ void bs_sub_stored_body(BsState *S, const z64 *part, 
     using T = typename BsVec<R>::t;
     z64 al;
     if constexpr (kFused) {
+        // a block without elements (a batch's grid is the largest lattice's) needs no alpha
+        if (blockIdx.x > 0 && (int64_t)blockIdx.x * blockDim.x >= n) return;
         if (!bs_alpha_body(S, part, nb, blockIdx.x == 0, al)) return;
     } else {
         if (S->h.done) return;
@@ -653,6 +658,10 @@ __device__ __forceinline__ void bs_res_stored_body(BsState *S, const z64 *opart,
     using T = typename BsVec<R>::t;
     z64 om;
     if constexpr (kFused) {
+        if (blockIdx.x > 0 && (int64_t)blockIdx.x * blockDim.x >= n) {  // no elements: nothing to scale, nothing to add
+            if (threadIdx.x < 2 && !S->h.done) part[2 * blockIdx.x + threadIdx.x] = {0.0, 0.0};
+            return;
+        }
         if (!bs_omega_body(S, opart, nb, blockIdx.x == 0, om)) return;
     } else {
         if (S->h.done) return;
@@ -1806,7 +1815,9 @@ void BsBatch::rebuild()
             desc[j].nb_s = stb_[ph][1].blocks(j);
             desc[j].nb_v = stb_[ph][3].blocks(j);
         }
-        fused_[ph] = 1;
+        int64_t blocks = 0;
+        for (int k : g) blocks += pr_[k]->nvb_;
+        fused_[ph] = blocks <= kBsFusedBlocks;
         for (const BsDesc &d : desc)
             for (int nb : {d.nb_s, d.nb_v})
                 if (partial_count(nb) * partial_width(nb) > kBsFusedPartials) fused_[ph] = 0;

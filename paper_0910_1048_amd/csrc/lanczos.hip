@@ -71,6 +71,9 @@ __global__ void lz_alpha_kernel(const z64 *partials, int nblk, LzScalars S, int 
 // Up to this many partials every block of the update adds them itself (one launch less per step: 2.4 us and a
 // gap on 8^4); above, the re-reads cost more than the launch of lz_alpha_kernel.
 constexpr int kLzFusedPartials = 1024;
+// in a batch, where the blocks come to the chip in turns and each adds the partials again, up to this many of them
+// (the figures are beside the same rule of the BiCGStab kernels, whose re-reads are these)
+constexpr int kLzFusedBlocks = 8192;
 
 __device__ __forceinline__ void lz_step_body(const z64 *partials, int nblk, const LzScalars &S, int j, double tol)
 {
@@ -112,18 +115,26 @@ __device__ __forceinline__ z64 ld2(const double2 *p, int64_t i)
 // One thread per pair of complex entries (e0 = 2*c2*V + s, e1 = e0 + V) so that
 // the FP32 stencil outputs ([6][V] float4) and FP64 vectors line up.  vc, wc (may be null): second
 // FP64 copies of vh_{j+1}, wh_{j+1} (the fixed stencil inputs of a lockstep batch).
-template <bool F32>
+template <bool F32, bool kFused>
 __device__ __forceinline__ void lz_update_body(const void *u_, const void *z_, const double2 *vj, const double2 *vjm,
                                                const double2 *wj, const double2 *wjm, double2 *vn, double2 *wn,
                                                float4 *vn32, float4 *wn32, double2 *vc, double2 *wc,
                                                const LzScalars &S, int j, int V /* component stride */,
                                                z64 *partials, const z64 *apart, int na)
 {
-    // coefficients of the two three-term recurrences (alpha_j from the na partials of apart, or with na = 0
-    // from the table)
+    const int64_t npair = (int64_t)6 * V;
+    if (kFused && blockIdx.x > 0 && (int64_t)blockIdx.x * blockDim.x >= npair) {
+        // no elements (a batch's grid is the largest lattice's): nothing to scale, nothing to add
+        if (threadIdx.x < 2) partials[2 * blockIdx.x + threadIdx.x] = {0.0, 0.0};
+        return;
+    }
+    // coefficients of the two three-term recurrences (kFused: alpha_j from the na partials of apart, else from
+    // the table)
     const double s0 = S.sv[j].r;
     const z64 t0 = S.tw[j];
-    const z64 al = na > 0 ? lz_alpha_body(apart, na, S, j, blockIdx.x == 0) : S.alpha[j];
+    z64 al;
+    if constexpr (kFused) al = lz_alpha_body(apart, na, S, j, blockIdx.x == 0);
+    else al = S.alpha[j];
     const z64 cu = {s0, 0.0};
     const z64 cv0 = -(s0 * al);
     const z64 cz = t0;
@@ -133,7 +144,6 @@ __device__ __forceinline__ void lz_update_body(const void *u_, const void *z_, c
         cv1 = -(S.sv[j - 1].r * S.hsup[j - 1]);       // h_{j-1,j} s_{j-1}
         cw1 = -(conj(S.hsub[j - 1]) * S.tw[j - 1]);   // conj(h_{j,j-1}) t_{j-1}
     }
-    const int64_t npair = (int64_t)6 * V;
     double a = 0.0, br = 0.0, bi = 0.0, c = 0.0;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npair; p += (int64_t)gridDim.x * blockDim.x) {
         const int c2 = (int)(p / V), s = (int)(p - (int64_t)c2 * V);
@@ -187,14 +197,14 @@ __device__ __forceinline__ void lz_update_body(const void *u_, const void *z_, c
         partials[2 * blockIdx.x + 1] = {v[2], v[3]};
     }
 }
-template <bool F32>
+template <bool F32, bool kFused>
 __global__ void __launch_bounds__(256) lz_update_kernel(const void *u_, const void *z_, const double2 *vj,
                                                         const double2 *vjm, const double2 *wj, const double2 *wjm,
                                                         double2 *vn, double2 *wn, float4 *vn32, float4 *wn32,
                                                         double2 *vc, double2 *wc, LzScalars S, int j, int V,
                                                         z64 *partials, const z64 *apart, int na)
 {
-    lz_update_body<F32>(u_, z_, vj, vjm, wj, wjm, vn, wn, vn32, wn32, vc, wc, S, j, V, partials, apart, na);
+    lz_update_body<F32, kFused>(u_, z_, vj, vjm, wj, wjm, vn, wn, vn32, wn32, vc, wc, S, j, V, partials, apart, na);
 }
 
 constexpr int kLiftChunk = 64;
@@ -500,12 +510,14 @@ extern "C" sgn_status sign_lanczos_2sided(sgn_lattice l, double mu, const void *
             const double2 *vjm = j > 0 ? reinterpret_cast<const double2 *>(Vj(j - 1)) : nullptr;
             const double2 *wjm = j > 0 ? reinterpret_cast<const double2 *>(Wj(j - 1)) : nullptr;
             if (f32)
-                hipLaunchKernelGGL(lz_update_kernel<true>, dim3(nvb), dim3(256), 0, s, u32.p, z32.p,
+                hipLaunchKernelGGL((na ? lz_update_kernel<true, true> : lz_update_kernel<true, false>), dim3(nvb), dim3(256),
+                                   0, s, u32.p, z32.p,
                                    (const double2 *)Vj(j), vjm, (const double2 *)Wj(j), wjm, (double2 *)vn,
                                    (double2 *)Wj(j + 1), (float4 *)v32.p, (float4 *)w32.p, (double2 *)nullptr,
                                    (double2 *)nullptr, S, j, (int)Sst, vpart, (const z64 *)part, na);
             else
-                hipLaunchKernelGGL(lz_update_kernel<false>, dim3(nvb), dim3(256), 0, s, u.p, z.p,
+                hipLaunchKernelGGL((na ? lz_update_kernel<false, true> : lz_update_kernel<false, false>), dim3(nvb), dim3(256),
+                                   0, s, u.p, z.p,
                                    (const double2 *)Vj(j), vjm, (const double2 *)Wj(j), wjm, (double2 *)vn,
                                    (double2 *)Wj(j + 1), (float4 *)nullptr, (float4 *)nullptr, (double2 *)nullptr,
                                    (double2 *)nullptr, S, j, (int)Sst, vpart, (const z64 *)part, na);
@@ -872,12 +884,12 @@ void QmrSolve::step(int j)
     const double2 *wjm = j > 0 ? reinterpret_cast<const double2 *>(Wj(j - 1)) : nullptr;
     const int pr = ctx_.prof_start(s_, SGN_K_SEED_UPDATE, true);
     if (f32)
-        launch_k(ctx_.prof_stamp(pr), lz_update_kernel<true>, dim3(nvb_), dim3(256), 0u, s_, u32_->p, z32_->p,
+        launch_k(ctx_.prof_stamp(pr), na ? lz_update_kernel<true, true> : lz_update_kernel<true, false>, dim3(nvb_), dim3(256), 0u, s_, u32_->p, z32_->p,
                            (const double2 *)basis[j], vjm, (const double2 *)Wj(j), wjm, (double2 *)basis[j + 1],
                            (double2 *)Wj(j + 1), (float4 *)v32_->p, (float4 *)w32_->p, (double2 *)nullptr,
                            (double2 *)nullptr, S_, j, (int)Sst_, vpart_, (const z64 *)part_, na);
     else
-        launch_k(ctx_.prof_stamp(pr), lz_update_kernel<false>, dim3(nvb_), dim3(256), 0u, s_, u, z, (const double2 *)basis[j],
+        launch_k(ctx_.prof_stamp(pr), na ? lz_update_kernel<false, true> : lz_update_kernel<false, false>, dim3(nvb_), dim3(256), 0u, s_, u, z, (const double2 *)basis[j],
                            vjm, (const double2 *)Wj(j), wjm, (double2 *)basis[j + 1], (double2 *)Wj(j + 1),
                            (float4 *)nullptr, (float4 *)nullptr, (double2 *)nullptr, (double2 *)nullptr, S_, j,
                            (int)Sst_, vpart_, (const z64 *)part_, na);
@@ -1088,18 +1100,18 @@ __global__ void __launch_bounds__(256) qb_alpha_batch(const QbDesc *d)
     lz_alpha_body(D.part1, D.nb1, D.S, *D.step, true);
 }
 
-template <bool F32>
-__global__ void __launch_bounds__(256) qb_update_batch(const QbDesc *d, int fused)
+template <bool F32, bool kFused>
+__global__ void __launch_bounds__(256) qb_update_batch(const QbDesc *d)
 {
     const QbDesc &D = d[blockIdx.y];
     if (*D.done) return;
     const int j = *D.step;
     const double2 *vj = static_cast<const double2 *>(D.slots[j]);
     const double2 *vjm = j > 0 ? static_cast<const double2 *>(D.slots[j - 1]) : nullptr;
-    lz_update_body<F32>(D.u, D.z, vj, vjm, D.W[j % 3], j > 0 ? D.W[(j + 2) % 3] : nullptr,
+    lz_update_body<F32, kFused>(D.u, D.z, vj, vjm, D.W[j % 3], j > 0 ? D.W[(j + 2) % 3] : nullptr,
                         static_cast<double2 *>(D.slots[j + 1]), D.W[(j + 1) % 3], D.v32, D.w32,
                         F32 ? nullptr : D.vcur, F32 ? nullptr : D.wcur, D.S, j, D.Sst, D.part2, D.part1,
-                        fused ? D.nb1 : 0);
+                                D.nb1);
 }
 
 // nb: the grid width of the update that wrote the partials
@@ -1218,7 +1230,9 @@ void QmrBatch::rebuild()
             desc[j].nb1 = stb_[ph][1].blocks(j);
             desc[j].slots = q.dslots_;
         }
-        fused_[ph] = 1;
+        int64_t blocks = 0;
+        for (int k : g) blocks += pr_[k]->nvb_;
+        fused_[ph] = blocks <= kLzFusedBlocks;
         for (const QbDesc &d : desc)
             if (partial_count(d.nb1) * partial_width(d.nb1) > kLzFusedPartials) fused_[ph] = 0;
         const size_t need = sizeof(QbDesc) * g.size();
@@ -1246,9 +1260,11 @@ void QmrBatch::launch_step(hipStream_t strm)
         stb_[ph][2].launch(strm);
         stb_[ph][3].launch(strm);
         if (ph >= 1)
-            hipLaunchKernelGGL(qb_update_batch<true>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d, fused);
+            hipLaunchKernelGGL((fused ? qb_update_batch<true, true> : qb_update_batch<true, false>), dim3(nvb_max_[ph], np),
+                               dim3(256), 0, strm, d);
         else
-            hipLaunchKernelGGL(qb_update_batch<false>, dim3(nvb_max_[ph], np), dim3(256), 0, strm, d, fused);
+            hipLaunchKernelGGL((fused ? qb_update_batch<false, true> : qb_update_batch<false, false>), dim3(nvb_max_[ph], np),
+                               dim3(256), 0, strm, d);
         hipLaunchKernelGGL(qb_step_batch, dim3(np), dim3(256), 0, strm, d, nvb_max_[ph]);
     }
     SGN_HIP(hipGetLastError());
