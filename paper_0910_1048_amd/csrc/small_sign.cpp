@@ -334,7 +334,9 @@ namespace {
 // closer to the exact one (k = 250: 2e-13 by the Schur form, 3e-16 here).
 
 constexpr int kPolesMinSize = 24;     // below, the Schur form costs microseconds
-constexpr int kPolesMax = 512;        // more poles (an eigenvalue near the imaginary axis): the Schur route
+// More poles than this (an eigenvalue near the imaginary axis): the Schur route.  A pole and its conjugate, twice,
+// take 13 k ns, the Schur form k^3 ns, so the limit grows with k^2 and stays below where they meet (k = 400: 5000).
+inline int poles_max(int k) { return std::max(512, (int)std::min<int64_t>((int64_t)k * k / 32, 1 << 20)); }
 constexpr double kPolesTruncation = 1e-20;  // |g_s(c lambda) - sign lambda| at every eigenvalue, below this
 constexpr double kPolesAgree = 1e-11;       // two evaluations with other poles agree to this, relative
 
@@ -493,7 +495,7 @@ void sign_poles(int k, const zc *diag, const zc *sub, const zc *sup, int s, doub
 // Returns true with sign(T) e_1 in y and the smallest |Re lambda| in *minre if
 //  - the QL iteration converges and its eigenvalues reproduce trace(T) and trace(T^2),
 //  - no eigenvalue is so near the imaginary axis (relative to its modulus and the spectrum's extent) that the
-//    truncation kPolesTruncation takes more than kPolesMax poles, and
+//    truncation kPolesTruncation takes more than poles_max poles, and
 //  - a second evaluation with another scale and more poles agrees to kPolesAgree.
 bool sign_by_poles(int k, const zc *diag, const zc *sub, const zc *sup, double tnorm, bool avx2, zc *y, double *minre)
 {
@@ -522,6 +524,7 @@ bool sign_by_poles(int k, const zc *diag, const zc *sub, const zc *sup, double t
     }
     if (!(std::abs(s1 - tr) <= 1e-10 * k * tnorm) || !(std::abs(s2 - tr2) <= 1e-10 * k * tnorm * tnorm)) return false;
     if (!(lo > 1e-8 * tnorm) || !std::isfinite(hi)) return false;
+    const int limit = poles_max(k);
     // |(1 - z)/(1 + z)| over z = c lambda in the right half plane (by the symmetry of g_s), c the mean of the circles
     auto poles = [&](double c) {
         double rho = 0.0;
@@ -529,13 +532,13 @@ bool sign_by_poles(int k, const zc *diag, const zc *sub, const zc *sup, double t
             const zc z = (l.real() > 0 ? c : -c) * l;
             rho = std::max(rho, std::norm(zc(1.0, 0.0) - z) / std::norm(zc(1.0, 0.0) + z));
         }
-        if (!(rho < 1.0)) return kPolesMax + 1;
+        if (!(rho < 1.0)) return limit + 1;
         const double need = std::log(0.5 * kPolesTruncation) / std::log(std::max(rho, 1e-6));  // rho = |.|^2: |.|^(2s)
-        return need < (double)kPolesMax ? std::max(8, (int)std::ceil(need)) : kPolesMax + 1;
+        return need < (double)limit ? std::max(8, (int)std::ceil(need)) : limit + 1;
     };
     const double c1 = 1.0 / std::sqrt(lo * hi), c2 = 1.07 * c1;
     const int n1 = poles(c1), n2 = poles(c2) + 4;
-    if (n1 > kPolesMax || n2 > kPolesMax) return false;
+    if (n1 > limit || n2 > limit) return false;
     std::vector<double> work;
     std::vector<zc> y1(k);
     sign_poles(k, diag, sub, sup, n1, c1, avx2, work, y1.data());
