@@ -129,7 +129,9 @@ sgn_status wilson_apply_dag(sgn_lattice lat, double mu, const void *in, void *ou
 
 /* wilson_apply without any device allocation, for callers that cannot allocate
  * (code under HIP graph capture, serving loops or harnesses that forbid
- * hipMalloc).  Same arguments, result and errors as wilson_apply; the
+ * hipMalloc).  Same arguments, result and errors as wilson_apply.  Canonical
+ * fields that are aligned to 16 bytes go through one kernel without staging
+ * unless the lattice is stored in the temporal gauge; otherwise the
  * canonical <-> internal staging of in and out uses one static device array of
  * SGN_NOALLOC_MAX_BYTES bytes per GPU (held by every GPU the library runs on
  * until the process ends) instead of per-lattice buffers, so a canonical-layout
@@ -260,7 +262,7 @@ typedef struct {
  *   Lanczos with A = H_W(mu), A^H = H_W(-mu), T_k tridiagonal,
  *   x = x_P + ||r|| V_k sign(T_k) e_1.
  * b, x: device, canonical complex128.  The small sign is evaluated on the host
- * in FP64 (complex Schur form); the call synchronises `stream`.  The basis
+ * in FP64 (see sgn_small_sign); the call synchronises `stream`.  The basis
  * vectors v_j (FP64) are taken from the context's pool as the steps proceed and
  * stay with the context after the call (memory follows the steps taken, at most
  * k vectors; SGN_ERR_NOMEM when one cannot be allocated).
@@ -275,8 +277,12 @@ sgn_status sign_lanczos_2sided(sgn_lattice lat, double mu, const void *b, void *
  * f(H_k) of the projected matrix), the routine sign_lanczos_2sided calls.
  * diag[k], sub[k-1] (T(i+1,i)) and sup[k-1] (T(i,i+1)) are interleaved
  * (re, im) doubles (sub, sup may be NULL when k = 1); y[k] receives the
- * result, by the complex Schur form of T (implicit single-shift QR, O(k^3)) and
- * the eigenvectors of its triangular factor.  *min_abs_re (may be NULL)
+ * result: from k = 24 on by the eigenvalues of T (implicit QL on the similar
+ * complex symmetric matrix) and the rational sign function with the poles that
+ * these need, a pair of tridiagonal solves each, O(k^2); where that cannot vouch
+ * for its result, and for smaller k, by the complex Schur form of T (implicit
+ * single-shift QR, O(k^3)) and the eigenvectors of its triangular factor.
+ * *min_abs_re (may be NULL)
  * receives min |Re lambda|.  SGN_ERR_INVALID for k < 1, NULL arrays or entries that are not finite,
  * SGN_ERR_IMAG_AXIS if |Re lambda| <= 1e-12 ||T||_inf for an eigenvalue,
  * SGN_ERR_BREAKDOWN if the QR iteration does not converge. */

@@ -9,9 +9,9 @@
 //
 // Per step j (all coefficients FP64, computed on the device):
 //   stencil  u  = A vh_j,    partials of wh_j^H u       (epilogue-fused dot)
-//   finalize alpha_j = conj(t_j) s_j wh_j^H u          (= w_j^H A v_j)
-//   stencil  z  = A^H wh_j
-//   update   vh_{j+1} = s_j u - alpha_j s_j vh_j - h_{j-1,j} s_{j-1} vh_{j-1}
+//   stencil  z  = A^H wh_j                              (on small lattices in the same launch)
+//   update   alpha_j = conj(t_j) s_j wh_j^H u          (= w_j^H A v_j; with many partials a launch of its own)
+//            vh_{j+1} = s_j u - alpha_j s_j vh_j - h_{j-1,j} s_{j-1} vh_{j-1}
 //            wh_{j+1} = t_j z - conj(alpha_j) t_j wh_j - conj(h_{j,j-1}) t_{j-1} wh_{j-1}
 //            partials of ||vh||^2, wh^H vh, ||wh||^2
 //   finalize h_{j+1,j} = ||vh_{j+1}||, s_{j+1} = 1/h_{j+1,j},

@@ -1,9 +1,11 @@
 // sign(T) e_1 for the small projected matrix of the direct two-sided Lanczos
 // method (section "Short recurrences": f(H_k) of the k x k projected matrix,
-// computed here through its eigendecomposition; the O(k^3) last term of the
-// cost proposition of the direct method, which dominates at small volumes).
+// the last term of the cost proposition of the direct method, which dominates at
+// small volumes if it is O(k^3)).
 //
-// Route: complex Schur form T = Z S Z^H by the implicit single-shift QR
+// First route: the eigenvalues alone and a rational function, O(k^2)
+// (sign_by_poles below).  Second route, for small k and where the first cannot
+// vouch for its result: complex Schur form T = Z S Z^H by the implicit single-shift QR
 // algorithm on the (tridiagonal, hence Hessenberg) input; eigenvectors of the
 // triangular S by back substitution; then
 //   sign(T) e_1 = Z X sign(Lambda) X^{-1} Z^H e_1,

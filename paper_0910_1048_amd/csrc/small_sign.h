@@ -8,7 +8,7 @@ namespace sgn {
 struct SmallSignInfo {
     double min_abs_re = 0.0;     // min |Re lambda| over the eigenvalues of T
     double norm = 0.0;           // infinity norm of T
-    double eigvec_growth = 0.0;  // largest 2-norm of a unit-diagonal eigenvector of the Schur factor
+    double eigvec_growth = 0.0;  // largest 2-norm of a unit-diagonal eigenvector of the Schur factor (0 if not formed)
 };
 
 // T(i,i) = diag[i], T(i+1,i) = sub[i], T(i,i+1) = sup[i] (i < k-1).
