@@ -1020,6 +1020,16 @@ __global__ void __launch_bounds__(64) bs_scatter_heads(BsState *const *S, const 
     for (int i = threadIdx.x; i < (int)(sizeof(BsHead) / 8); i += blockDim.x) dst[i] = src[i];
 }
 
+// New entries of the slot tables of a batch's problems, written together.
+struct BsSlotWrite {
+    void **at;
+    void *slot;
+};
+__global__ void __launch_bounds__(256) bs_write_slots(const BsSlotWrite *w, int n)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) *w[i].at = w[i].slot;
+}
+
 // Stored-basis slots handed out from the context's per-size pools; shared by the problems of a
 // lockstep batch (each takes the next unused buffers) together with one byte budget.
 struct BsSlotPools {
@@ -1081,6 +1091,7 @@ class BsStored {
     std::vector<char> rf32_, sf32_;
     BsSlotPools own_pools_;
     BsSlotPools *pools_;
+    std::vector<BsSlotWrite> *table_writes_ = nullptr;  // set: new table entries go here, not to the device
     int phase_ = 0, launched_ = 0, reliable_ = 0;
     hipGraphExec_t gexec_ = nullptr;
     // state of run() between its steps
@@ -1131,7 +1142,9 @@ void *BsStored::take_slot(size_t bytes)
 // r-slots 0 .. upto + 1 and s-slots 0 .. upto; slots first written in the FP32 phase hold FP32 vectors.  Small
 // vectors: when the tables grow, slots for up to kBsSlotsAhead further iterations are taken along as far as the
 // pool has unused buffers (an FP32 vector may then sit in an FP64-sized one), since each growth costs two copies
-// that the stream waits for (with one growth per poll 1800 copies, 8 of 115 ms, in a batch of 24 problems).
+// that the stream waits for.  (A batch writes the new entries of all its problems at once instead: one growth per
+// problem and poll was 1800 copies, 8 of 115 ms, with 24 problems, and what one problem had taken ahead another had
+// to allocate.)
 void BsStored::ensure_slots(int upto)
 {
     const size_t r0 = rslots_.size(), s0 = sslots_.size();
@@ -1139,7 +1152,12 @@ void BsStored::ensure_slots(int upto)
     while ((int)rslots_.size() < upto + 2) rslots_.push_back(take_slot(bytes));
     while ((int)sslots_.size() < upto + 1) sslots_.push_back(take_slot(bytes));
     if (rslots_.size() == r0 && sslots_.size() == s0) return;
-    if (b64_ <= kBsAheadBytes && o_.basis_slots == 0) {
+    if (table_writes_) {
+        for (size_t i = r0; i < rslots_.size(); ++i) table_writes_->push_back({rtab_ + i, rslots_[i]});
+        for (size_t i = s0; i < sslots_.size(); ++i) table_writes_->push_back({stab_ + i, sslots_[i]});
+        return;
+    }
+    if (pools_ == &own_pools_ && b64_ <= kBsAheadBytes && o_.basis_slots == 0) {
         const size_t last = std::min<size_t>(maxiter_ + poll_, (size_t)upto + kBsSlotsAhead);
         const std::vector<void *> &pool = ctx_.basis_pools[bytes];
         while (rslots_.size() < last + 2 && sslots_.size() < last + 1 && pools_->next[bytes] + 2 <= pool.size() &&
@@ -1929,11 +1947,26 @@ sgn_status BsBatch::run(sgn_stats *st)
     z64 *dru = static_cast<z64 *>(dru_->p);
     bool dirty = true;
     int finished_since = 0;
+    const size_t nwrite = (size_t)np * (2 * poll_ + 3);  // a poll's new entries of every problem
+    DeviceScratch dwrites(sizeof(BsSlotWrite) * nwrite);
+    std::vector<BsSlotWrite> writes;
     std::vector<BsHead> heads(pr_.size());
     std::vector<int> rus;
     while (active > 0) {
+        writes.clear();
         for (auto &p : pr_)
-            if (!p->done_) p->ensure_slots(p->launched_ + poll_);
+            if (!p->done_) {
+                p->table_writes_ = &writes;
+                p->ensure_slots(p->launched_ + poll_);
+                p->table_writes_ = nullptr;
+            }
+        for (size_t i = 0; i < writes.size(); i += nwrite) {
+            const int n = (int)std::min(nwrite, writes.size() - i);
+            SGN_HIP(hipMemcpyAsync(dwrites.p, writes.data() + i, sizeof(BsSlotWrite) * n, hipMemcpyHostToDevice, s_));
+            hipLaunchKernelGGL(bs_write_slots, dim3((n + 255) / 256), dim3(256), 0, s_,
+                               static_cast<const BsSlotWrite *>(dwrites.p), n);
+            SGN_HIP(hipGetLastError());
+        }
         if (dirty) {
             rebuild();
             dirty = false;
