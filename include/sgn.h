@@ -177,8 +177,9 @@ typedef struct {
  * block sizes (whole x-rows or x-y planes within the LDS budget, under site caps
  * of 576, 432, 384, 288, 192 and 96), each as one t-slice and, for even L_t, as a
  * brick of two, for nrhs = 1 also the kernel without LDS staging (block_sites 0; for
- * lattices whose field is at most 9 MiB, and then for every nrhs, this is the kernel
- * that splits a site's eight hops over eight wavefronts, the untuned default there),
+ * lattices whose field is at most 9 MiB this is the kernel that splits a site's eight hops
+ * over eight wavefronts, the untuned default there, also tried for nrhs fields of together
+ * at most 9 MiB; launches of more fields take the default staged shape if it was chosen),
  * and with FP16 two-row links and nrhs > 1 both link modes -- is
  * applied reps times (0: 20) to zero fields on `stream` and timed
  * with HIP events; the fastest is kept in the context and used by every later
@@ -194,7 +195,7 @@ sgn_status sgn_autotune(sgn_lattice lat, sgn_prec p, int nrhs, int reps, sgn_tun
  * single-RHS form, 1: the multi-RHS form) by hand, as sgn_autotune would: blocks of at most
  * max_sites sites (0: no cap beyond the LDS budget and the launch bound; -1: the kernel without
  * LDS staging, one launch per right-hand side in the multi-RHS form, or on small lattices the
- * split kernel, see sgn_autotune), t_slices = 1 or 2
+ * split kernel for up to 9 MiB of fields, see sgn_autotune), t_slices = 1 or 2
  * (bricks of two t-slices, even L_t), links_in_registers = -1 (default), 0 or 1 (multi-RHS form
  * with FP16 two-row links).  For replaying a saved tuning result or pinning a shape.
  * SGN_ERR_INVALID if no staged block of that shape fits the lattice.  Synchronises the device. */

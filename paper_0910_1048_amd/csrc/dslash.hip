@@ -1317,16 +1317,35 @@ namespace {
 // 8.4 / 9.3, 70200 sites 9.4 / 10.3, 16^3 x 32 14.0 / 12.5.
 constexpr int64_t kSplitMaxBytes = 9 << 20;
 
-bool split_fits(const Lattice &lat, sgn_prec p)
+// nr fields of the lattice together
+bool split_takes(const Lattice &lat, sgn_prec p, int nr)
 {
-    return lat.V * (p == SGN_PREC_F64 ? 192 : 96) <= kSplitMaxBytes;
+    return nr * lat.V * (p == SGN_PREC_F64 ? 192 : 96) <= kSplitMaxBytes;
 }
+
+bool split_fits(const Lattice &lat, sgn_prec p) { return split_takes(lat, p, 1); }
 
 bool use_split(const Lattice &lat, sgn_prec p, bool multi)
 {
     if (!split_fits(lat, p)) return false;
     auto it = lat.ctx->tuned.find({lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, multi ? 1 : 0});
     return it == lat.ctx->tuned.end() || it->second.unstaged;
+}
+
+// The staged shape set for a lattice.  Where the split kernel serves the lattice's own applications, `unstaged`
+// stands for that kernel and says nothing about launches of more fields than it takes: the default shape there,
+// so that they stay one launch (without it each problem of a batch took a launch of its own).
+Context::TunedShape staged_shape(const Lattice &lat, sgn_prec p, bool multi)
+{
+    Context::TunedShape ts = lat.ctx->tuned_shape(lat.L, p, multi);
+    if (ts.unstaged && split_fits(lat, p)) ts.unstaged = ts.max_sites = 0, ts.tslices = 1;
+    return ts;
+}
+
+// whether a staged shape (or the unstaged kernel on a large lattice) was set for the multi-RHS form
+bool multi_shape_set(const Lattice &lat, sgn_prec p)
+{
+    return lat.ctx->tuned.count({lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, 1}) && !use_split(lat, p, true);
 }
 
 // Everything about one stencil application except the launch itself.
@@ -1440,7 +1459,7 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
         P.nblk_sites = (int)((lat.V + kSplitSites - 1) / kSplitSites);
         ps.nblk = P.nblk_sites + (int)((lat.S - lat.V + kSplitThreads - 1) / kSplitThreads);
     } else {
-        const Context::TunedShape ts = lat.ctx->tuned_shape(lat.L, p, nr > 1);
+        const Context::TunedShape ts = staged_shape(lat, p, nr > 1);
         if (!ts.unstaged) {
             ps.pl = staged_plan(lat, p, max_threads, ts.max_sites, ts.tslices);
             if (!ps.pl.ok && ts.tslices == 2) ps.pl = staged_plan(lat, p, max_threads, ts.max_sites, 1);
@@ -1542,7 +1561,7 @@ bool link_regs(const Lattice &lat, sgn_prec p)
 {
     if (p != SGN_PREC_F32_H16 || lat.link_ne != 6) return false;
     const char *e = std::getenv("SGN_MULTI_LINK_REGS");
-    return !(e && e[0] == '0') && lat.ctx->tuned_shape(lat.L, p, true).regs != 0;
+    return !(e && e[0] == '0') && staged_shape(lat, p, true).regs != 0;
 }
 
 // 2..16 right-hand sides without an epilogue in one launch; false if no kernel takes them together
@@ -1550,11 +1569,10 @@ bool launch_rhs_block(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, 
                       void *const *out, hipStream_t s)
 {
     const std::vector<Epilogue> ep(nr);
-    const bool small = (double)nr * lat.V * (p == SGN_PREC_F64 ? 192 : 96) <= (double)kSplitMaxBytes;
-    const KernelPick pick = small && use_split(lat, p, true) ? kSplit : kStaged;
+    const KernelPick pick = split_takes(lat, p, nr) && use_split(lat, p, true) ? kSplit : kStaged;
     bool regs = pick == kStaged && link_regs(lat, p);
     int cap = regs ? kRegsMaxThreads : 0;
-    if (regs && !lat.ctx->tuned.count({lat.L[0], lat.L[1], lat.L[2], lat.L[3], (int)p, 1})) {
+    if (regs && !multi_shape_set(lat, p)) {
         // Two waves per SIMD hide little latency: below 1024 blocks half the block is faster where it fills its
         // wavefronts as well (12 right-hand sides, 512 against 256 sites per block: 16^4 59 against 53 us,
         // 16^3 x 32 98 against 91), and slower where it does not (20^4, 400 of 448 against 200 of 256 lanes: 141
@@ -1727,7 +1745,7 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
             if (l == lats.size()) {
                 lats.push_back(j.lat);
                 cnt.push_back(0);
-                const Context::TunedShape ts = j.lat->ctx->tuned_shape(j.lat->L, p, true);
+                const Context::TunedShape ts = staged_shape(*j.lat, p, true);
                 const StagedPlan pl = staged_plan(*j.lat, p, 0, ts.max_sites, ts.tslices);
                 per_staged.push_back(pl.ok ? pl.nblk_sites : (j.lat->V + 255) / 256);
                 per.push_back(small && use_split(*j.lat, p, true) ? (j.lat->V + kSplitSites - 1) / kSplitSites
@@ -1770,7 +1788,7 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
     for (size_t g = 0; g < groups.size(); ++g) regs_ = regs_ && jobs[groups[g][0]].lat->link_ne == 6;
     {
         const char *e = std::getenv("SGN_MULTI_LINK_REGS");
-        const int tuned = jobs.empty() ? -1 : jobs[0].lat->ctx->tuned_shape(jobs[0].lat->L, p, true).regs;
+        const int tuned = jobs.empty() ? -1 : staged_shape(*jobs[0].lat, p, true).regs;
         regs_ = regs_ && multi && !(e && e[0] == '0') && tuned != 0;
     }
     const int cap = regs_ ? kRegsMaxThreads : 0;
@@ -2022,8 +2040,8 @@ extern "C" sgn_status sgn_autotune(sgn_lattice l, sgn_prec p, int nrhs, int reps
             int unstaged;
         };
         std::vector<Cand> cands;
-        // the unstaged kernel, or on small lattices the split one (also for several right-hand sides)
-        if (!multi || split_fits(lat, p)) cands.push_back({0, 0, 1, -1, 0.0, 1});
+        // the unstaged kernel, or on small lattices the split one (for several right-hand sides if it takes them)
+        if (!multi || split_takes(lat, p, nrhs)) cands.push_back({0, 0, 1, -1, 0.0, 1});
         const bool can_regs = multi && p == SGN_PREC_F32_H16 && lat.link_ne == 6;
         for (int regs : can_regs ? std::vector<int>{1, 0} : std::vector<int>{-1}) {
             for (int T : {1, 2}) {

@@ -1,0 +1,91 @@
+"""Launches of several right-hand sides on lattices whose shape was tuned to the kernel without LDS staging (on
+small lattices the split kernel): above the 9 MiB of fields that it takes they stay one launch, with the same bits."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_0910_1048_amd as sgn  # noqa: E402
+from gpu_util import dev, host  # noqa: E402
+
+CLASS = {sgn.F64: "stencil_f64", sgn.F32: "stencil_f32", sgn.F32_H16: "stencil_h16"}
+CDT = {sgn.F64: np.complex128, sgn.F32: np.complex64, sgn.F32_H16: np.complex64}
+
+
+def _calls(c, name, fn):
+    sgn.sgn_profile_enable(c, True)
+    try:
+        r = fn()
+        torch.cuda.synchronize()
+        return sgn.sgn_profile_read(c)[name]["calls"], r
+    finally:
+        sgn.sgn_profile_enable(c, False)
+
+
+def _split_chosen(lat):
+    """as sgn_autotune leaves it where the split kernel was the fastest, for one and for several right-hand sides"""
+    for p in CLASS:
+        sgn.sgn_tune_set(lat, p, False, -1, 1)
+        sgn.sgn_tune_set(lat, p, True, -1, 1)
+
+
+# (lattices, problems on each): groups of several right-hand sides, and groups of one beside an untuned lattice;
+# FP64 fields of 18.9 and 13.4 MB together, and 4.0 MB for the split kernel
+@pytest.mark.parametrize("dims,nprob,tuned", [([(8, 8, 8, 8)], 24, [0]), ([(8, 8, 8, 8), (16, 16, 16, 16)], 1, [0]),
+                                              ([(8, 8, 8, 8), (12, 12, 4, 4)], 2, [0, 1])])
+@pytest.mark.parametrize("solver", [sgn.multishift_bicgstab, sgn.multishift_solve, sgn.multishift_qmr])
+def test_solver_batches_stay_batched(dims, nprob, tuned, solver):
+    c = sgn.Context(0)
+    lats = [sgn.Lattice(c, dev(synth.gauge_field(d, 0.3, 3)), d, 0.15) for d in dims]
+    rf = sgn.sgn_rational_neuberger(8, 0.3, 2.3)
+    src = [(lat, 0.02 * k, dev(synth.gaussian_source(d, k).ravel())) for lat, d in zip(lats, dims) for k in range(nprob)]
+
+    def solve():
+        probs = [sgn.Problem(lat, mu, b, torch.empty_like(b)) for lat, mu, b in src]
+        solver(probs, rf, tol=1e-8, prec=sgn.F64)
+        return [p.x for p in probs]
+
+    calls, first = _calls(c, CLASS[sgn.F64], solve)
+    for k in tuned:
+        _split_chosen(lats[k])
+    calls2, again = _calls(c, CLASS[sgn.F64], solve)
+    assert calls2 == calls
+    for x, y in zip(first, again):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32, sgn.F32_H16])
+@pytest.mark.parametrize("nrhs", [2, 16])
+def test_blocks_of_right_hand_sides_stay_one_launch(prec, nrhs):
+    dims = (12, 12, 12, 12)   # 4.0 and 2.0 MB a field: two fit the split kernel, sixteen do not
+    c = sgn.Context(0)
+    lat = sgn.Lattice(c, dev(synth.gauge_field(dims, 0.3, 3)), dims, 0.15)
+    nb = lat.spinor_bytes(prec)
+    x = [torch.empty(nb, dtype=torch.uint8, device="cuda") for _ in range(nrhs)]
+    for j, t in enumerate(x):
+        sgn.sgn_spinor_pack(lat, dev(synth.gaussian_source(dims, j).astype(CDT[prec])), t, prec)
+    mus = [0.05 * j for j in range(nrhs)]
+
+    def apply():
+        y = [torch.empty_like(t) for t in x]
+        sgn.wilson_apply_multi(lat, mus, x, y, prec)
+        return y
+
+    calls, first = _calls(c, CLASS[prec], apply)
+    _split_chosen(lat)
+    calls2, again = _calls(c, CLASS[prec], apply)
+    assert calls == 1 and calls2 == 1
+    for a, b in zip(first, again):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("nrhs,offered", [(1, True), (2, True), (16, False)])
+def test_the_split_kernel_is_offered_for_the_fields_that_it_takes(nrhs, offered):
+    dims = (12, 12, 12, 12)
+    c = sgn.Context(0)
+    lat = sgn.Lattice(c, dev(synth.gauge_field(dims, 0.3, 3)), dims, 0.15)
+    cands = sgn.sgn_autotune(lat, sgn.F32, nrhs, reps=2)
+    assert any(k["block_sites"] == 0 for k in cands) == offered
