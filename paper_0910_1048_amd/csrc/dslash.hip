@@ -2083,7 +2083,9 @@ extern "C" sgn_status sgn_autotune(sgn_lattice l, sgn_prec p, int nrhs, int reps
         hipEvent_t e0, e1;
         SGN_HIP(hipEventCreate(&e0));
         SGN_HIP(hipEventCreate(&e1));
-        const Context::TunedShape before = ctx.tuned_shape(lat.L, p, multi);
+        const auto set = ctx.tuned.find(key);
+        const bool was_set = set != ctx.tuned.end();
+        const Context::TunedShape before = was_set ? set->second : Context::TunedShape{};
         try {
             for (Cand &c : cands) {
                 ctx.tuned[key] = {c.cap, c.regs, c.T, c.unstaged};
@@ -2098,7 +2100,9 @@ extern "C" sgn_status sgn_autotune(sgn_lattice l, sgn_prec p, int nrhs, int reps
                 c.us = 1e3 * ms / reps;
             }
         } catch (...) {
-            ctx.tuned[key] = before;
+            // (an entry where there was none would keep the split kernel from lattices of these dimensions)
+            if (was_set) ctx.tuned[key] = before;
+            else ctx.tuned.erase(key);
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             throw;

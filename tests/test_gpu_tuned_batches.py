@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 import paper_0910_1048_amd as sgn  # noqa: E402
-from gpu_util import dev, host  # noqa: E402
+from gpu_util import dev  # noqa: E402
 
 CLASS = {sgn.F64: "stencil_f64", sgn.F32: "stencil_f32", sgn.F32_H16: "stencil_h16"}
 CDT = {sgn.F64: np.complex128, sgn.F32: np.complex64, sgn.F32_H16: np.complex64}
@@ -89,3 +89,26 @@ def test_the_split_kernel_is_offered_for_the_fields_that_it_takes(nrhs, offered)
     lat = sgn.Lattice(c, dev(synth.gauge_field(dims, 0.3, 3)), dims, 0.15)
     cands = sgn.sgn_autotune(lat, sgn.F32, nrhs, reps=2)
     assert any(k["block_sites"] == 0 for k in cands) == offered
+
+
+def test_a_refused_autotune_leaves_the_lattice_untuned():
+    """A lattice without FP32 links cannot be tuned for FP32; the other lattices of its dimensions keep the split
+    kernel, which runs the two applications of a Lanczos step in one launch."""
+    dims = (8, 8, 8, 8)
+    c = sgn.Context(0)
+    U = dev(synth.gauge_field(dims, 0.3, 3))
+    lat = sgn.Lattice(c, U, dims, 0.15)
+    only64 = sgn.Lattice(c, U, dims, 0.15, prec_mask=1 << sgn.F64)
+    b = dev(synth.gaussian_source(dims, 1).ravel())
+
+    def solve():
+        x = torch.empty_like(b)
+        sgn.sign_lanczos_2sided(lat, 0.1, b, x, k=20, prec=sgn.F32)
+        return x
+
+    calls, first = _calls(c, CLASS[sgn.F32], solve)
+    with pytest.raises(sgn.SgnError):
+        sgn.sgn_autotune(only64, sgn.F32, 1, reps=2)
+    calls2, again = _calls(c, CLASS[sgn.F32], solve)
+    assert calls2 == calls
+    assert torch.equal(first, again)
