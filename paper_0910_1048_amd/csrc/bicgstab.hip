@@ -35,6 +35,7 @@
 #include <complex>
 #include <vector>
 
+#include "basis_slots.h"
 #include "field_io.h"
 #include "launch.h"
 #include "vec.h"
@@ -1030,13 +1031,6 @@ __global__ void __launch_bounds__(256) bs_write_slots(const BsSlotWrite *w, int 
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) *w[i].at = w[i].slot;
 }
 
-// Stored-basis slots handed out from the context's per-size pools; shared by the problems of a
-// lockstep batch (each takes the next unused buffers) together with one byte budget.
-struct BsSlotPools {
-    std::map<size_t, size_t> next;  // next unused buffer of each per-size pool
-    double budget = 0.0, used = 0.0;
-};
-
 constexpr int kBsSlotsAhead = 64;
 constexpr size_t kBsAheadBytes = 16 << 20;
 
@@ -1087,7 +1081,7 @@ class BsStored {
     BsState *S_ = nullptr;
     BsHist *hist_ = nullptr;
     void **rtab_ = nullptr, **stab_ = nullptr;  // device slot tables (r_k, s_k)
-    std::vector<void *> rslots_, sslots_;
+    BsSlotTables slots_;
     std::vector<char> rf32_, sf32_;
     BsSlotPools own_pools_;
     BsSlotPools *pools_;
@@ -1123,8 +1117,6 @@ class BsStored {
 // a slot buffer of the given size (FP64 or FP32 vector) from the context's pools
 void *BsStored::take_slot(size_t bytes)
 {
-    if (pools_->used + (double)bytes > pools_->budget)
-        throw Failure{SGN_ERR_NOMEM, "multishift_bicgstab: stored basis exceeds its budget (basis_slots)"};
     auto &pool = ctx_.basis_pools[bytes];
     size_t &next = pools_->next[bytes];
     if (next == pool.size()) {
@@ -1135,7 +1127,6 @@ void *BsStored::take_slot(size_t bytes)
         }
         pool.push_back(b);
     }
-    pools_->used += (double)bytes;
     return pool[next++];
 }
 
@@ -1147,31 +1138,25 @@ void *BsStored::take_slot(size_t bytes)
 // to allocate.)
 void BsStored::ensure_slots(int upto)
 {
-    const size_t r0 = rslots_.size(), s0 = sslots_.size();
+    std::vector<void *> &rs = slots_.r, &ss = slots_.s;
+    const size_t r0 = rs.size(), s0 = ss.size();
     const size_t bytes = lo() ? b32_ : b64_;
-    while ((int)rslots_.size() < upto + 2) rslots_.push_back(take_slot(bytes));
-    while ((int)sslots_.size() < upto + 1) sslots_.push_back(take_slot(bytes));
-    if (rslots_.size() == r0 && sslots_.size() == s0) return;
+    auto take = [this](size_t n) { return take_slot(n); };
+    if (!slots_.need(upto, bytes, *pools_, take))
+        throw Failure{SGN_ERR_NOMEM, "multishift_bicgstab: stored basis exceeds its budget (basis_slots)"};
+    if (rs.size() == r0 && ss.size() == s0) return;
     if (table_writes_) {
-        for (size_t i = r0; i < rslots_.size(); ++i) table_writes_->push_back({rtab_ + i, rslots_[i]});
-        for (size_t i = s0; i < sslots_.size(); ++i) table_writes_->push_back({stab_ + i, sslots_[i]});
+        for (size_t i = r0; i < rs.size(); ++i) table_writes_->push_back({rtab_ + i, rs[i]});
+        for (size_t i = s0; i < ss.size(); ++i) table_writes_->push_back({stab_ + i, ss[i]});
         return;
     }
-    if (pools_ == &own_pools_ && b64_ <= kBsAheadBytes && o_.basis_slots == 0) {
-        const size_t last = std::min<size_t>(maxiter_ + poll_, (size_t)upto + kBsSlotsAhead);
-        const std::vector<void *> &pool = ctx_.basis_pools[bytes];
-        while (rslots_.size() < last + 2 && sslots_.size() < last + 1 && pools_->next[bytes] + 2 <= pool.size() &&
-               pools_->used + 2.0 * (double)bytes <= 0.5 * pools_->budget) {
-            rslots_.push_back(take_slot(bytes));
-            sslots_.push_back(take_slot(bytes));
-        }
-    }
-    if (rslots_.size() > r0)
-        SGN_HIP(hipMemcpy(rtab_ + r0, rslots_.data() + r0, sizeof(void *) * (rslots_.size() - r0),
-                          hipMemcpyHostToDevice));
-    if (sslots_.size() > s0)
-        SGN_HIP(hipMemcpy(stab_ + s0, sslots_.data() + s0, sizeof(void *) * (sslots_.size() - s0),
-                          hipMemcpyHostToDevice));
+    if (pools_ == &own_pools_ && b64_ <= kBsAheadBytes && o_.basis_slots == 0)
+        slots_.ahead(std::min<size_t>(maxiter_ + poll_, (size_t)upto + kBsSlotsAhead), bytes,
+                     ctx_.basis_pools[bytes].size(), *pools_, take);
+    if (rs.size() > r0)
+        SGN_HIP(hipMemcpy(rtab_ + r0, rs.data() + r0, sizeof(void *) * (rs.size() - r0), hipMemcpyHostToDevice));
+    if (ss.size() > s0)
+        SGN_HIP(hipMemcpy(stab_ + s0, ss.data() + s0, sizeof(void *) * (ss.size() - s0), hipMemcpyHostToDevice));
 }
 
 void BsStored::launch_iteration(hipStream_t strm)
@@ -1271,7 +1256,7 @@ void BsStored::reliable_update(BsHead &h)
     SGN_HIP(hipGetLastError());
     const int k = h.iter;
     convert_64_to_32(t64_, r32_, Sst_, s_);
-    SGN_HIP(hipMemcpyAsync(rslots_[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
+    SGN_HIP(hipMemcpyAsync(slots_.r[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
     rf32_[k] = 1;
     h.rho = dot_sync(ctx_, rh32_, r32_, n_, true, s_);
     h.rnorm = norm_sync(ctx_, r32_, n_, true, s_);
@@ -1293,7 +1278,7 @@ void BsStored::reliable_update_async(int k, z64 *out)
     hipLaunchKernelGGL(bs_addto64, dim3(nvb_), dim3(256), 0, s_, (const double2 *)y_, (double2 *)t64_, n_);
     SGN_HIP(hipGetLastError());
     convert_64_to_32(t64_, r32_, Sst_, s_);
-    SGN_HIP(hipMemcpyAsync(rslots_[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
+    SGN_HIP(hipMemcpyAsync(slots_.r[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
     rf32_[k] = 1;
     // the same reductions as dot_sync / norm_sync, left on the device (stream order lets the
     // context's partials be reused by the next problem)
@@ -1320,8 +1305,8 @@ void BsStored::switch_phase(BsHead &h, int to)
         // the current residual's slot becomes FP32 (what the FP32 iteration reads); p and the
         // shadow vector move to FP32
         const int k = h.iter;
-        convert_64_to_32(rslots_[k], r32_, Sst_, s_);
-        SGN_HIP(hipMemcpyAsync(rslots_[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
+        convert_64_to_32(slots_.r[k], r32_, Sst_, s_);
+        SGN_HIP(hipMemcpyAsync(slots_.r[k], r32_, b32_, hipMemcpyDeviceToDevice, s_));
         rf32_[k] = 1;
         convert_64_to_32(p64_, p32_, Sst_, s_);
         convert_64_to_32(rh64_, rh32_, Sst_, s_);
@@ -1344,11 +1329,11 @@ void BsStored::lift(int K, const std::vector<zc> &cr, const std::vector<zc> &cs,
     std::vector<BsSlot> sl;
     std::vector<z64> cf;
     for (int j = 0; j <= K; ++j) {
-        sl.push_back(BsSlot{rslots_[j], j < (int)rf32_.size() ? rf32_[j] : 0, 0});
+        sl.push_back(BsSlot{slots_.r[j], j < (int)rf32_.size() ? rf32_[j] : 0, 0});
         cf.push_back({cr[j].real(), cr[j].imag()});
     }
     for (int j = 0; j < K; ++j) {
-        sl.push_back(BsSlot{sslots_[j], j < (int)sf32_.size() ? sf32_[j] : 0, 0});
+        sl.push_back(BsSlot{slots_.s[j], j < (int)sf32_.size() ? sf32_[j] : 0, 0});
         cf.push_back({cs[j].real(), cs[j].imag()});
     }
     const int nk = (int)sl.size();
@@ -1374,8 +1359,8 @@ void BsStored::lift_multi(int K, const std::vector<const std::vector<zc> *> &cr,
     SGN_REQUIRE(nout >= 1 && nout <= kLiftOut && (int)cr.size() == nout && (int)cs.size() == nout,
                 "multishift_bicgstab: lift sets");
     std::vector<BsSlot> sl;
-    for (int j = 0; j <= K; ++j) sl.push_back(BsSlot{rslots_[j], j < (int)rf32_.size() ? rf32_[j] : 0, 0});
-    for (int j = 0; j < K; ++j) sl.push_back(BsSlot{sslots_[j], j < (int)sf32_.size() ? sf32_[j] : 0, 0});
+    for (int j = 0; j <= K; ++j) sl.push_back(BsSlot{slots_.r[j], j < (int)rf32_.size() ? rf32_[j] : 0, 0});
+    for (int j = 0; j < K; ++j) sl.push_back(BsSlot{slots_.s[j], j < (int)sf32_.size() ? sf32_[j] : 0, 0});
     const int nk = (int)sl.size();
     std::vector<z64> cf((size_t)nk * kLiftOut, z64{0.0, 0.0});
     for (int o = 0; o < nout; ++o) {
@@ -1488,7 +1473,7 @@ bool BsStored::setup(char *a, sgn_stats *stp)
     ensure_slots(poll_);
     rf32_.assign(1, 0);
     for (char *v : {rh64_, p64_}) SGN_HIP(hipMemcpyAsync(v, y_, b64_, hipMemcpyDeviceToDevice, s_));
-    SGN_HIP(hipMemcpyAsync(rslots_[0], y_, b64_, hipMemcpyDeviceToDevice, s_));
+    SGN_HIP(hipMemcpyAsync(slots_.r[0], y_, b64_, hipMemcpyDeviceToDevice, s_));
     hipLaunchKernelGGL(bs_fill_kernel<double2>, dim3(nvb_), dim3(256), 0, s_, (double2 *)x64_, make_double2(0.0, 0.0),
                        n_);
     SGN_HIP(hipGetLastError());
