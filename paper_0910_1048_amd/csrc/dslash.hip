@@ -432,6 +432,10 @@ template <typename R> constexpr int kStagedMaxThreads = sizeof(R) == 8 ? 512 : 7
 // the multi-RHS form with the links in registers (FP16 links): 8 waves per block at most, so
 // up to 256 VGPRs (two waves per SIMD)
 constexpr int kRegsMaxThreads = 512;
+// the split kernel leaves one partial sum per wavefront of such a block, or of the unstaged kernel's
+static_assert((std::max(kStagedMaxThreads<float>, kStagedMaxThreads<double>) + 63) / 64 <= kMaxPartialWidth &&
+                  (SGN_STENCIL_THREADS + 63) / 64 <= kMaxPartialWidth,
+              "the readers of the partial sums add kMaxPartialWidth entries at most");
 
 template <typename R>
 __device__ __forceinline__ void lds_store_spinor(SpT<R> *l, int B, int i, const cpx<R> v[12]);

@@ -222,8 +222,13 @@ struct Epilogue {
 // entry with Epilogue::norm), to be added in that order, packed into one int.  width > 1 where the launch wrote
 // one entry per wavefront of what is one block in the staged kernel: the sums then have the same bits
 // whichever kernel ran.
-constexpr int kMaxPartialWidth = 11;
-inline int pack_partials(int n, int width) { return n | (width - 1) << 24; }
+constexpr int kMaxPartialWidth = 11;  // wavefronts of the largest block; the readers take no wider sum
+inline int pack_partials(int n, int width)
+{
+    if (n < 0 || n > 0xFFFFFF || width < 1 || width > kMaxPartialWidth)
+        throw Failure{SGN_ERR_INVALID, "stencil: too many partial sums"};
+    return n | (width - 1) << 24;
+}
 __host__ __device__ inline int partial_count(int p) { return p & 0xFFFFFF; }
 __host__ __device__ inline int partial_width(int p) { return (p >> 24) + 1; }
 
