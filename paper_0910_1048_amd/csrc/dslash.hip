@@ -206,6 +206,19 @@ __device__ __forceinline__ void link_mul(const cpx<R> u[9], const cpx<R> h[6], c
 template <typename R>
 using SpT = typename SpinorStore<R>::type;
 
+// One component's terms of the partial sums conj(w) . out and ||out||^2, in FP64.  The products are contracted here
+// and not by the compiler, in one place for every kernel, so that the sums have the same bits whichever one runs
+// (the order within a term differs between the precisions, as it always has).
+template <typename R>
+__device__ __forceinline__ void dot_terms(cpx<R> w, cpx<R> out, double &dr, double &di, double &dn)
+{
+    constexpr bool kRealFirst = sizeof(R) == 8;
+    const z64 a = cast<double>(w), o = cast<double>(out);
+    dr += kRealFirst ? fma(a.i, o.i, a.r * o.r) : fma(a.r, o.r, a.i * o.i);
+    di += fma(a.r, o.i, -(a.i * o.r));
+    dn += kRealFirst ? fma(o.i, o.i, o.r * o.r) : fma(o.r, o.r, o.i * o.i);
+}
+
 // Output side of one site: gamma5 on the result, the epilogue
 // out = a * in_scale * Op(in) + b * z, the store, and the site's terms of the
 // partial sums conj(w) . out and ||out||^2 (FP64).  The scales are real unless
@@ -264,12 +277,7 @@ __device__ __forceinline__ void finish_site(cpx<R> (&acc)[12], const RhsParams &
                 load_spinor(static_cast<const SpT<R> *>(Q.w), S, s, ww);
             }
 #pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                z64 a = cast<double>(ww[k]), o = cast<double>(acc[k]);
-                dr += a.r * o.r + a.i * o.i;
-                di += a.r * o.i - a.i * o.r;
-                dn += o.r * o.r + o.i * o.i;
-            }
+            for (int k = 0; k < 12; ++k) dot_terms<R>(ww[k], acc[k], dr, di, dn);
         }
     }
 }
@@ -1080,20 +1088,8 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx,
             if (dots && Q.w) {
                 double v[3] = {0.0, 0.0, 0.0};
                 if (valid) {
-                    // the products contracted as the compiler contracts finish_site's sums, which it does in
-                    // the other order for FP64
-                    constexpr bool kRealFirst = sizeof(R) == 8;
-                    double dr = 0.0, di = 0.0, dn = 0.0;
 #pragma unroll
-                    for (int k = 0; k < 12; ++k) {
-                        const z64 a = cast<double>(ww[k]), o = cast<double>(out_lds[lane * 13 + k]);
-                        dr += kRealFirst ? fma(a.i, o.i, a.r * o.r) : fma(a.r, o.r, a.i * o.i);
-                        di += fma(a.r, o.i, -(a.i * o.r));
-                        dn += kRealFirst ? fma(o.i, o.i, o.r * o.r) : fma(o.r, o.r, o.i * o.i);
-                    }
-                    v[0] = dr;
-                    v[1] = di;
-                    v[2] = dn;
+                    for (int k = 0; k < 12; ++k) dot_terms<R>(ww[k], out_lds[lane * 13 + k], v[0], v[1], v[2]);
                 }
 #pragma unroll
                 for (int k = 0; k < 3; ++k) v[k] = wave_sum(v[k]);
