@@ -102,6 +102,7 @@ const char *sgn_last_error(void);
 #define SGN_LINKS_TEMPORAL_GAUGE 0x200u
 sgn_status sgn_lattice_create(sgn_handle h, const sgn_lattice_desc *d, const void *links,
                               unsigned prec_mask, void *stream, sgn_lattice *out);
+/* (also after sgn_finalize of its context) */
 sgn_status sgn_lattice_destroy(sgn_lattice lat);
 /* sites V and bytes of one spinor in the internal layout for precision p */
 int64_t sgn_lattice_volume(sgn_lattice lat);

@@ -486,6 +486,7 @@ extern "C" sgn_status sgn_lattice_create(sgn_handle h, const sgn_lattice_desc *d
         SGN_HIP(hipSetDevice(ctx->device));
         lat = new Lattice();
         lat->ctx = ctx;
+        lat->device = ctx->device;
         for (int i = 0; i < 4; ++i) {
             lat->L[i] = d->dims[i];
             lat->bc[i] = d->bc[i];
@@ -570,7 +571,7 @@ extern "C" sgn_status sgn_lattice_destroy(sgn_lattice l)
     return guard([&] {
         if (!l) return;
         Lattice *lat = as_lattice(l);
-        SGN_HIP(hipSetDevice(lat->ctx->device));
+        SGN_HIP(hipSetDevice(lat->device));
         for (void *p : {lat->links64, lat->links32, lat->links16, lat->gauge, lat->stage_in, lat->stage_out})
             if (p) SGN_HIP(hipFree(p));
         delete lat;

@@ -165,6 +165,7 @@ struct Context {
 
 struct Lattice {
     Context *ctx = nullptr;
+    int device = 0;  // the context's: a garbage collector may release the context first
     int L[4] = {0, 0, 0, 0};
     int bc[4] = {1, 1, 1, -1};
     double kappa = 0.0;
