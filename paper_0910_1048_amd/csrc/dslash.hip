@@ -1025,7 +1025,6 @@ __device__ __forceinline__ void split_body(const StencilParams &P, const int bx,
             }
         }
         __syncthreads();
-        double dr = 0.0, di = 0.0, dn = 0.0;
         if (mine) {
             const cpx<R> *chi = chi_lds + lane;
             switch (wave) {
@@ -1363,6 +1362,8 @@ struct PreparedStencil {
 
 enum KernelPick { kAuto, kStaged, kSplit };
 
+bool has_epilogue(const Epilogue &e) { return e.w || e.z || e.a != 1.0 || e.in_scale; }
+
 // max_threads > 0 caps the staged block (the register-link multi-RHS form)
 PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in,
                                 void *const *out, const Epilogue *ep, int max_threads = 0, KernelPick pick = kAuto)
@@ -1401,7 +1402,7 @@ PreparedStencil prepare_stencil(const Lattice &lat, sgn_prec p, int nr, const Op
         Q.norm = ep[r].norm ? 1 : 0;
         if (ep[r].w && !ep[r].partials) throw Failure{SGN_ERR_INVALID, "stencil dot without partial buffer"};
         ps.dot = ps.dot || ep[r].w != nullptr;
-        ps.epi = ps.epi || ep[r].w != nullptr || ep[r].z != nullptr || ep[r].a != 1.0 || ep[r].in_scale != nullptr;
+        ps.epi = ps.epi || has_epilogue(ep[r]);
         // an epilogue operand counts once: a dot partner equal to z is not read again
         extra_bytes += (ep[r].z ? sb : 0.0) + (ep[r].w && ep[r].w != ep[r].z ? sb : 0.0);
         extra_flops += (ep[r].z ? 96.0 : 0.0) + (ep[r].w ? 96.0 : 0.0) + 24.0;
@@ -1606,13 +1607,12 @@ bool launch_rhs_block(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, 
 int launch_multi(const Lattice &lat, sgn_prec p, int nr, const OpSpec *op, const void *const *in, void *const *out,
                  const Epilogue *ep, hipStream_t s, bool canon)
 {
+    if (nr > 1 && std::none_of(ep, ep + nr, has_epilogue) && launch_rhs_block(lat, p, nr, op, in, out, s)) return 0;
     const PreparedStencil ps = prepare_stencil(lat, p, nr, op, in, out, ep, 0, canon ? kSplit : kAuto);
-    if (nr > 1) {
-        if (!ps.epi && !ps.dot && launch_rhs_block(lat, p, nr, op, in, out, s)) return ps.partials;
-        if (ps.split || ps.pl.ok) {
-            for (int r = 0; r < nr; ++r) launch_multi(lat, p, 1, op + r, in + r, out + r, ep + r, s, false);
-            return ps.partials;
-        }
+    if (nr > 1 && (ps.split || ps.pl.ok)) {
+        int partials = 0;  // the same for each
+        for (int r = 0; r < nr; ++r) partials = launch_multi(lat, p, 1, op + r, in + r, out + r, ep + r, s, false);
+        return partials;
     }
     // one launch unless the unstaged kernel runs several right-hand sides
     const int prof = lat.ctx->prof_start(s, kclass(p), ps.pl.ok || nr == 1);
