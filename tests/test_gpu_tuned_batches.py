@@ -1,5 +1,7 @@
-"""Launches of several right-hand sides on lattices whose shape was tuned to the kernel without LDS staging (on
-small lattices the split kernel): above the 9 MiB of fields that it takes they stay one launch, with the same bits."""
+"""Batches at the limits of their launch rules.  Launches of several right-hand sides on lattices whose shape was tuned
+to the kernel without LDS staging (on small lattices the split kernel): above the 9 MiB of fields that it takes they
+stay one launch, with the same bits.  Batches with a pinned shape beside an untuned one, and on either side of the
+8192 vector blocks up to which the scalar steps are part of the vector kernels."""
 import numpy as np
 import pytest
 
@@ -112,3 +114,54 @@ def test_a_refused_autotune_leaves_the_lattice_untuned():
     calls2, again = _calls(c, CLASS[sgn.F32], solve)
     assert calls2 == calls
     assert torch.equal(first, again)
+
+
+@pytest.mark.parametrize("prec", [sgn.F64, sgn.F32, sgn.F32_H16])
+@pytest.mark.parametrize("solver", [sgn.multishift_bicgstab, sgn.multishift_solve, sgn.multishift_qmr])
+def test_split_and_staged_groups_in_one_batch(solver, prec):
+    """A lattice with a pinned staged shape beside one on the split kernel: two launches per stencil step, and the
+    bits of the batch that is all on the split kernel (the pinned shape is the one whose sums that kernel leaves)."""
+    c = sgn.Context(0)
+    dims = [(8, 8, 8, 8), (12, 12, 4, 4)]
+    lats = [sgn.Lattice(c, dev(synth.gauge_field(d, 0.3, 3)), d, 0.15) for d in dims]
+    rf = sgn.sgn_rational_neuberger(8, 0.3, 2.3)
+    src = [(lat, 0.02 * k, dev(synth.gaussian_source(d, k).ravel())) for k in range(2) for lat, d in zip(lats, dims)]
+
+    def solve():
+        probs = [sgn.Problem(lat, mu, b, torch.empty_like(b)) for lat, mu, b in src]
+        st = solver(probs, rf, tol=1e-8, prec=prec)
+        return [p.x for p in probs], [k["iterations"] for k in st]
+
+    first, its = solve()
+    for p in CLASS:
+        sgn.sgn_tune_set(lats[0], p, False, 0, 1)
+        sgn.sgn_tune_set(lats[0], p, True, 0, 1)
+    again, its2 = solve()
+    assert its == its2
+    for x, y in zip(first, again):
+        assert torch.equal(x, y)
+
+
+# 16^4: 1024 vector blocks a problem, the most that one takes
+@pytest.mark.parametrize("nprob", [8, 9])
+@pytest.mark.parametrize("solver,prec", [(sgn.multishift_bicgstab, sgn.F64), (sgn.multishift_bicgstab, sgn.F32),
+                                         (sgn.multishift_qmr, sgn.F64), (sgn.multishift_qmr, sgn.F32)])
+def test_either_side_of_the_fused_scalar_steps_in_a_batch(solver, prec, nprob):
+    c = sgn.Context(0)
+    dims = (16, 16, 16, 16)
+    lat = sgn.Lattice(c, dev(synth.gauge_field(dims, 0.3, 3)), dims, 0.15)
+    rf = sgn.sgn_rational_neuberger(8, 0.3, 2.3)
+    src = [(0.02 * k, dev(synth.gaussian_source(dims, k).ravel())) for k in range(nprob)]
+
+    def solve(which):
+        probs = [sgn.Problem(lat, mu, b, torch.empty_like(b)) for mu, b in which]
+        st = solver(probs, rf, tol=1e-10, prec=prec)
+        return [p.x for p in probs], [k["iterations"] for k in st]
+
+    xs, its = solve(src)
+    for k in (0, nprob - 1):
+        x, it = solve(src[k:k + 1])
+        if prec == sgn.F64 and solver is sgn.multishift_bicgstab:  # the same sums in the same order
+            assert torch.equal(xs[k], x[0]) and it[0] == its[k]
+        # else: the solvers' tolerance, times ten for its being a residual's, twice
+        assert torch.linalg.norm(xs[k] - x[0]) <= 2e-9 * torch.linalg.norm(x[0])
