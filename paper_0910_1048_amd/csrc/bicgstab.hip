@@ -534,9 +534,13 @@ __device__ __forceinline__ void stz_nt(float2 *p, int64_t e, z64 v)
 // All of them are bound by latency: the loads (the flags, the partials and, in the thread of each shift, that
 // shift's state) are issued before the first use.
 constexpr int kBsFusedPartials = 1024;
-// A batch's blocks do not all fit the chip at once, and each adds the partials again: 24 problems on 8^4, 12^4 and
-// 16^4 (25,700 blocks with work), FP32: s and r' updates 47 + 58 us fused, 37 + 41 and two launches apart.
-constexpr int kBsFusedBlocks = 8192;
+// In a batch the limit is also the blocks that the chip holds at once, eight on each of 256 CUs: beyond them the
+// blocks come in turns and each adds the partials again.  Solves with the scalars fused against apart, by the vector
+// blocks of all problems (8^4, 12^4 and 16^4, median of three runs): FP64 1160: 8.2 / 8.5 ms, 1930: 10.9 / 10.9,
+// 2048: 15.8 / 15.7, 3860: 18.9 / 18.6, 5840: 17.1 / 16.7; FP32 1160: 8.9 / 9.5, 1540: 10.3 / 10.8, 2048: 13.7 / 13.5,
+// 2920: 9.8 / 9.6, 3890: 13.3 / 12.8, 5840: 15.8 / 15.2.  24 problems on 8^4, 12^4 and 16^4 (17,700 blocks), FP32: s
+// and r' updates 47 + 58 us fused, 37 + 41 and two launches apart.
+constexpr int kBsFusedBlocks = 2048;
 static_assert(kBsShifts <= 256, "one thread per shift in the 256-thread scalar kernels");
 
 // alpha = rho / r^^H v from the dotting stencil's partials; the BiCG factors zeta_next (writer: this block

@@ -71,9 +71,11 @@ __global__ void lz_alpha_kernel(const z64 *partials, int nblk, LzScalars S, int 
 // Up to this many partials every block of the update adds them itself (one launch less per step: 2.4 us and a
 // gap on 8^4); above, the re-reads cost more than the launch of lz_alpha_kernel.
 constexpr int kLzFusedPartials = 1024;
-// in a batch, where the blocks come to the chip in turns and each adds the partials again, up to this many of them
-// (the figures are beside the same rule of the BiCGStab kernels, whose re-reads are these)
-constexpr int kLzFusedBlocks = 8192;
+// In a batch up to the blocks that the chip holds at once (eight on each of 256 CUs), beyond which the blocks come in
+// turns and each adds the partials again.  QMR batches fused against apart, by the update's blocks of all problems
+// (median of three runs): FP64 970: 12.4 / 12.7 ms, 1550: 28.1 / 28.8, 2330: 40.1 / 40.6, 3900: 54.3 / 54.0, 7790:
+// 107.3 / 105.2; FP32 780: 15.4 / 16.0, 1550: 26.5 / 27.3, 3900: 48.6 / 48.4, 8190: 97.4 / 94.8.
+constexpr int kLzFusedBlocks = 2048;
 
 __device__ __forceinline__ void lz_step_body(const z64 *partials, int nblk, const LzScalars &S, int j, double tol)
 {
