@@ -737,11 +737,10 @@ __global__ void __launch_bounds__(kRegs ? kRegsMaxThreads : kStagedMaxThreads<R>
 // link, all in flight at once, and leaves the transported half spinor in LDS; after the barrier six
 // wavefronts take one pair of components of the 64 sites each, add the eight hops to the diagonal term in
 // the order and with the operations of the staged kernel (so the result has the same bits) and run the
-// epilogue.  Neighbours come through L2: no reuse inside the block.  One FP64 application on 8^4: 8.7 us as
-// 16 staged blocks, 4.6 us here.
-// The form for canonical fields is used at every size: it is as fast as the staged kernel on internal fields
-// (24^3 x 48: FP64 146 us against 135, FP32 61 against 58) and needs no pack and unpack passes (with them 267
-// and 130 us).
+// epilogue.  Neighbours come through L2: no reuse inside the block.  One FP64 application on 8^4: 7.7 us as
+// 16 staged blocks, 4.1 us here.
+// The form for canonical fields is used at every size: on 24^3 x 48 it is 5-8% behind the staged kernel on internal
+// fields (FP64 146 us against 135, FP32 61 against 58) and needs no pack and unpack passes (with them 267 and 130 us).
 constexpr int kSplitSites = 64, kSplitThreads = 512;
 
 // component pair C (components 2C, 2C + 1) of site s, internal layout
@@ -1311,9 +1310,10 @@ namespace {
 
 // Internal fields up to this size take the split kernel unless a staged shape was tuned or pinned for their
 // lattice (49152 FP64 or 98304 FP32 sites): beyond it the chip is full either way and the staged kernel's
-// reuse of neighbours wins.  One application, split against the best staged shape: 4^4 FP64 4.1 / 6.7 us,
-// 8^4 4.6 / 7.6, 12^4 7.5 / 9.8, 40320 sites 10.0 / 11.0, 16^4 15.1 / 14.5; FP32 8^4 3.9 / 6.8, 16^4
-// 8.4 / 9.3, 70200 sites 9.4 / 10.3, 16^3 x 32 14.0 / 12.5.
+// reuse of neighbours wins.  One application of many in a row, split / default staged / best staged shape, us:
+// FP64 4^4 3.8 / 6.9 / 6.4, 8^4 4.1 / 7.7 / 6.8, 12^4 5.8 / 10.2 / 8.0, 40320 sites 9.3 / 11.7 / 9.5, 49152
+// 10.5 / 10.9 / 10.9, 16^4 13.1 / 12.6 / 12.6, 70200 15.5 / 14.6 / 14.3; FP32 8^4 3.5 / 7.4 / 6.4, 16^4
+// 7.8 / 9.1 / 8.4, 70200 8.3 / 10.3 / 8.9, 98304 9.9 / 9.7 / 9.7, 16^3 x 32 13.0 / 10.6 / 10.6 (FP16 links as FP32).
 constexpr int64_t kSplitMaxBytes = 9 << 20;
 
 // nr fields of the lattice together
@@ -1791,6 +1791,9 @@ void StencilBatch::prepare(const std::vector<StencilJob> &jobs, sgn_prec p)
         const int tuned = jobs.empty() ? -1 : staged_shape(*jobs[0].lat, p, true).regs;
         regs_ = regs_ && multi && !(e && e[0] == '0') && tuned != 0;
     }
+    // The full block, also where half of it would be faster (FP16 launches of BiCGStab batches, full against half:
+    // 24 on 16^4 106 / 102 us, 12 on 16^3 x 32 102 / 97, 8 on 20^4 110 / 94, 32 on 12^4 60 / 60): the block decides
+    // how the dot products are summed, and with it the iterates of a mixed solve.
     const int cap = regs_ ? kRegsMaxThreads : 0;
     // the blocks whose sums a split dot product leaves (without a staged shape for some lattice every
     // application would be a launch of its own, without the cap)
