@@ -1333,7 +1333,8 @@ bool use_split(const Lattice &lat, sgn_prec p, bool multi)
 
 // The staged shape set for a lattice.  Where the split kernel serves the lattice's own applications, `unstaged`
 // stands for that kernel and says nothing about launches of more fields than it takes: the default shape there,
-// so that they stay one launch (without it each problem of a batch took a launch of its own).
+// so that they stay one launch.  Without it each took a launch of its own: on tuned lattices 32 FP64 solves on 8^4 in
+// one call 76.6 ms, now 30.5 (untuned 30.6); 16 FP32 right-hand sides on 12^4 95 us, now 46.
 Context::TunedShape staged_shape(const Lattice &lat, sgn_prec p, bool multi)
 {
     Context::TunedShape ts = lat.ctx->tuned_shape(lat.L, p, multi);
